@@ -20,10 +20,12 @@
  * Method: ADMM in the ReLU-QP style (Sec. IV-B) -- one Cholesky-factorised
  * KKT matrix per grasp shared by all of its wrenches, an affine step plus a
  * clamp per iteration, periodic residual checks with per-grasp step-size
- * adaptation -- followed by an FP64 polish that re-solves the reduced KKT
- * system on the identified active set and corrects that set with dual
- * active-set steps, keeping the polished point only when its KKT conditions
- * hold.
+ * adaptation -- followed by an FP64 polish to the exact minimiser.  For the
+ * pyramid with gamma = 0 that is a semismooth Newton method on the QP's
+ * six-dimensional dual; what it leaves, and the other forms, go to a polish
+ * that re-solves the reduced KKT system on the identified active set and
+ * corrects that set with dual active-set steps, keeping the polished point
+ * only when its KKT conditions hold.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -113,8 +115,13 @@ typedef struct {
     float rho_max;
     float rho_hysteresis; /* refactor only when rho changes by this factor    */
     float fp64_cond;      /* factor K in FP64 when cond estimate exceeds this */
-    int polish_steps;     /* cap on active-set corrections in the polish      */
-    int polish_chunk;     /* factorisations a QP takes in the one-lane FP64   */
+    int polish_steps;     /* cap on the steps of the polish (Newton steps;    */
+                          /* active-set corrections)                          */
+    int polish_chunk;     /* 0 = the one-lane active-set polish; otherwise    */
+                          /* the pyramid with gamma = 0 and eps_reg >= 5e-7   */
+                          /* takes the dual Newton polish.  Where that does   */
+                          /* not apply: factorisations a QP takes in the      */
+                          /* one-lane FP64                                    */
                           /* polish before it is handed to the contact-       */
                           /* parallel polish (a group of lanes, one per       */
                           /* contact); 0 = every polish ends in the one-lane  */

@@ -23,6 +23,7 @@
 #include "bodex_cone.h"
 #include "bodex_gpolish.h"
 #include "bodex_math.h"
+#include "bodex_newton.h"
 
 namespace bodex {
 
@@ -94,7 +95,24 @@ struct KArgs {
     SpillPtrs spill;
     int* spill_count;
     int* spill_idx;
+    // dual Newton polish: per QP the dual solution u [6][W] and the result
+    // word (bodex_newton_kernels.h: bit 0 solved), and the number of QPs left;
+    // fin_mode 3: the finalize launch handles those alone
+    double* nu;
+    int* ninfo;
+    int* nfail;
 };
+// Word of ninfo: bit 0 solved, bit 1 not to be solved (non-finite input), 2-9
+// Newton steps, 10-17 evaluations, 18-31 line-search slopes.
+constexpr int kNewtonOk = 1, kNewtonSkip = 2;
+__device__ inline int newton_info(const NewtonOut& o) {
+    return int((o.ok ? 1u : 0u) | unsigned(min(o.steps, 255)) << 2 | unsigned(min(o.evals, 255)) << 10 |
+               unsigned(min(o.slopes, 16383)) << 18);
+}
+__device__ inline double newton_info_flops(int m, int info) {
+    const unsigned v = unsigned(info);
+    return (v >> 10) & 255 ? newton_flops(m, (v >> 2) & 255, (v >> 10) & 255, v >> 18) : 0.0;
+}
 
 struct SlotInfo {
     int g, m, s, w0;
@@ -744,7 +762,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
     static_assert(MODE == 0 || !GAM, "the chunked polish has no normal-sum row");
     constexpr int mode = MODE;
     __shared__ int sTile;
-    for (int t = fetch_tile(a, &sTile, -1); t < a.n_tiles; t = fetch_tile(a, &sTile, t)) {
+    const bool rest = mode == 0 && !GAM && a.fin_mode == 3;  // only what the Newton method left
+    if (rest && *a.nfail == 0) return;
+    for (int t = fetch_tile(a, &sTile, -1); t < a.n_tiles; t = rest ? t + int(gridDim.x) : fetch_tile(a, &sTile, t)) {
         int nsl;
         load_slots(a, t, P.info, nsl);
         int slot, j;
@@ -753,6 +773,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
         SlotInfo si = {0, 0, 1, 0};
         if (act) si = P.info[slot];
         const int w = si.w0 + j;
+        const bool left = rest && act && !(a.ninfo[w] & kNewtonOk);
+        if (rest && !__syncthreads_or(left)) continue;
         // this lane's spill record (-1: none)
         int kspill = (act && mode == 2) ? a.spill_idx[w] : -1;
         if (mode == 2 && !__syncthreads_or(kspill >= 0)) continue;  // nothing handed on in this tile
@@ -796,6 +818,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
                     po.picks = a.spill.iv(kSpPicks, kspill);
                     ran = true;
                 }
+            } else if (rest && !left) {
+                skip = true;
             } else if (finite_in && a.polish) {
                 PolishState<MM> PS;
                 PS.S.pc = S.pc;
@@ -841,7 +865,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
             if (mode == 1) a.spill_idx[w] = kspill;
             if (!skip) {
                 if (ran) {
-                    if (a.pflops) a.pflops[w] = float(polish_flops(si.m, po));
+                    if (a.pflops)
+                        a.pflops[w] = float(polish_flops(si.m, po) + (rest ? newton_info_flops(si.m, a.ninfo[w]) : 0.0));
                     if (po.status == 0) {
                         polished = true;
                         st |= kStPolished;
@@ -938,17 +963,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
                 a.status[w] = st;
                 a.kkt[w] = float(rel);
                 a.qobj[w] = float(Q);
-            } else if (mode == 2) {
+            } else if (mode == 2 || rest) {
                 Q = double(a.qobj[w]);  // finished in the first pass
             }
-            if (kspill >= 0) atomicOr(&P.flag[slot], 8);
+            if (kspill >= 0 || left) atomicOr(&P.flag[slot], 8);
         }
         P.red[lane] = Q;
         __syncthreads();
         // energies: in the first pass of grasps with nothing handed on, in
         // the second of the others
         const bool handed = act && (P.flag[slot] & 8);
-        if (act && j == 0 && (mode == 0 || (mode == 1 && !handed) || (mode == 2 && handed))) {
+        if (act && j == 0 && (rest ? handed : (mode == 0 || (mode == 1 && !handed) || (mode == 2 && handed)))) {
             double E = 0.0;
             for (int l = lane; l < lane + si.s; ++l) E += P.red[l];
             a.energy[si.g] = float(E);

@@ -14,6 +14,9 @@ hipError_t launch_reset(int* q, int n, hipStream_t st);
 // (KArgs::spill); group size (lanes per QP) for a kernel size.
 hipError_t launch_gpolish(int mm, const KArgs& a, int grid, hipStream_t st);
 int gpolish_group(int mm);
+// Dual Newton polish of every QP (gs lanes each) and the outputs of the solved
+// ones.
+hipError_t launch_newton(int mm, int gs, const KArgs& a, hipStream_t st);
 // Circular-cone form (KArgs::cone set).
 hipError_t launch_admm_cone(int mm, int occ, const KArgs& a, int grid, size_t lds, hipStream_t st);
 hipError_t launch_finalize_cone(int mm, const KArgs& a, int grid, size_t lds, hipStream_t st);

@@ -372,12 +372,37 @@ hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStrea
     return a.cone ? bodex::launch_backward_cone(mm, a, grid, lds, st) : bodex::launch_backward(mm, a, grid, lds, st);
 }
 
+// Dual Newton polish (bodex_newton.h): for the pyramid without the normal-sum
+// row, unless polish_chunk 0 asks for the one-lane kernel.  eps at least
+// 5e-7: the method's forces carry the rounding of |beta t| / eps (1e-16 of 1e6
+// at the default 1e-6); below that the active-set polish, which works in the
+// forces, is the more accurate one.
+bool newton_applies(const bodex_qp_params& p) {
+    return (p.flags & BODEX_F_POLISH) && p.friction_cone == BODEX_CONE_PYRAMID8 && p.gamma == 0.f &&
+           p.polish_chunk != 0 && p.polish_steps > 0 && p.eps_reg >= 5e-7f;
+}
+
+// Lanes per QP.  More lanes shorten the chain of a QP's steps, fewer waste
+// less on the replicated factor and on idle contact lanes.  Measured, solve +
+// outputs, us at 8 / 4 / 2 lanes: 5 contacts 16,384 QPs 243 / 239 / 313,
+// 32,768 358 / 316 / 320, 131,072 899 / 806 / 688, 262,144 1658 / 1434 / 1142
+// (6 contacts alike); 4 contacts (4 / 2 lanes) 32,766 QPs 256 / 283, 98,304
+// 491 / 471, 262,140 1075 / 930; 8 contacts 16,379 QPs 263 / 266 / 342, 65,527
+// 589 / 525 / 571, 131,065 1011 / 873 / 911.
+int newton_group(int mm, int n_qps) {
+    if (mm <= 4) return n_qps <= 65536 ? 4 : 2;
+    if (n_qps <= 20480) return 8;
+    return mm <= 6 && n_qps > 40960 ? 2 : 4;
+}
+
 // Chunked polish (the factorisation budget polish_chunk, -1: by batch
 // size): the one-lane pass hands QPs that need more factorisations to the
 // contact-parallel polish.  Sets up the record workspace (records for every
 // QP of the batch, so none is ever finished in the first pass for want of
 // room) in a; chunked is false where the chunked polish does not apply (no
 // polish, the circular cone, gamma > 0, chunk 0: effective()).
+// The dual Newton polish takes u and a result word per QP from the same
+// workspace (less than the records need).
 int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, bool& chunked, int& grid_g) {
     const int chunk = effective(h->prm, W).polish_chunk;
     chunked = chunk > 0;
@@ -387,6 +412,12 @@ int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, bool& chunked, int& grid_g
     const size_t nd = size_t(3 * mm + 3) * K, ni = size_t(bodex::kSpInts) * K + size_t(W);
     const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, nd * sizeof(double) + ni * sizeof(int));
     if (rc) return rc;
+    if (newton_applies(h->prm)) {
+        a.nu = static_cast<double*>(h->d_spill);
+        a.ninfo = reinterpret_cast<int*>(a.nu + 6 * K);
+        chunked = false;
+        return 0;
+    }
     a.spill.d = static_cast<double*>(h->d_spill);
     a.spill.i = reinterpret_cast<int*>(a.spill.d + nd);
     a.spill.K = int(K);
@@ -404,7 +435,13 @@ int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, bool& chunked, int& grid_g
 int enqueue_finalize(bodex_qp* h, KArgs f, int mm, bool chunked, int* d_queue, int grid_f, int grid_g,
                      size_t lds_f) {
     f.queue = nullptr;
-    if (chunked) {
+    if (f.nu) {
+        f.nfail = d_queue + 2;
+        const int gs = newton_group(mm, f.W);
+        HIP_TRY(h, bodex::launch_newton(mm, gs, f, h->stream));
+        f.fin_mode = 3;
+        HIP_TRY(h, launch(Kind::Fin, mm, f, std::min(grid_f, 1024), lds_f, h->stream));
+    } else if (chunked) {
         f.spill_count = d_queue + 1;
         f.fin_mode = 1;
         HIP_TRY(h, launch(Kind::Fin, mm, f, grid_f, lds_f, h->stream));
@@ -760,10 +797,10 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
 
     bool chunked = false;
     int grid_g = 0;
+    const size_t n_ints = desc_ints(G, S, lay);
     rc = chunk_setup(h, a, W, mm, chunked, grid_g);
     if (rc) return rc;
 
-    const size_t n_ints = desc_ints(G, S, lay);
     const bool timing = (h->prm.flags & BODEX_F_TIMING) != 0;
     const bool graph = (h->prm.flags & BODEX_F_GRAPH) != 0 && h->stream != nullptr;
     const size_t lds_a = admm_lds(mm, S.slots);
@@ -806,7 +843,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
         if (rc) return rc;
         rc = enqueue(h->d_desc, timing);
         if (rc) return rc;
-        h->last_launches = chunked ? 5 : 3;
+        h->last_launches = (a.nu || chunked) ? 5 : 3;
         h->t_admm = h->t_fin = timing;
         return 0;
     }
@@ -1263,7 +1300,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
         if (rc) return rc;
         rc = enqueue(h->d_desc);
         if (rc) return rc;
-        h->last_launches = 2 + (chunked ? 7 : 5) * d->iters;
+        h->last_launches = 2 + ((a.nu || chunked) ? 7 : 5) * d->iters;
         return 0;
     }
     // Graph path: the descent's launches captured once per shape, pointers
