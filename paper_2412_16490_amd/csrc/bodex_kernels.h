@@ -1108,7 +1108,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
     const ConeWork<LaneVec> W(LaneVec{work + lane, kWave}, LaneVec{work + NV * kWave + lane, kWave},
                               LaneVec{work + 2 * NV * kWave + lane, kWave}, LaneVec{work + 3 * NV * kWave + lane, kWave});
     __shared__ int sTile;
-    for (int t = fetch_tile(a, &sTile, -1); t < a.n_tiles; t = fetch_tile(a, &sTile, t)) {
+    const bool rest = !GAM && a.fin_mode == 3;  // only what the Newton method left
+    if (rest && *a.nfail == 0) return;
+    for (int t = fetch_tile(a, &sTile, -1); t < a.n_tiles; t = rest ? t + int(gridDim.x) : fetch_tile(a, &sTile, t)) {
         int nsl;
         load_slots(a, t, P.info, nsl);
         int slot, j;
@@ -1116,10 +1118,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
         const bool act = slot >= 0;
         SlotInfo si = {0, 0, 1, 0};
         if (act) si = P.info[slot];
-        const bool good = fin_setup<MM>(a, P, nsl, slot, j, si, true);
         const int w = si.w0 + j;
+        const bool left = rest && act && !(a.ninfo[w] & kNewtonOk);
+        if (rest && !__syncthreads_or(left)) continue;
+        const bool good = fin_setup<MM>(a, P, nsl, slot, j, si, true);
         double Q = 0.0;
-        if (act) {
+        if (rest && act && !left) {
+            Q = double(a.qobj[w]);
+        } else if (act) {
             const double* Gs = P.G + size_t(slot) * NG;
             const size_t W_ = size_t(a.sW);  // state stride
             const size_t sw = state_col(a, si, j);
@@ -1154,7 +1160,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
                     e1 = po.evals;
                     g1 = po.grads;
                 }
-                if (a.pflops) a.pflops[w] = float(cone_polish_flops(si.m, po));
+                if (a.pflops)
+                    a.pflops[w] = float(cone_polish_flops(si.m, po) +
+                                        (rest ? newton_info_flops(si.m, a.ninfo[w]) : 0.0));
                 if (po.status == 0) {
                     polished = true;
                     st |= kStPolished;
@@ -1234,10 +1242,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
             a.status[w] = st;
             a.kkt[w] = float(rel);
             a.qobj[w] = float(Q);
+            if (left) atomicOr(&P.flag[slot], 8);
         }
         P.red[lane] = Q;
         __syncthreads();
-        if (act && j == 0) {
+        if (act && j == 0 && (!rest || (P.flag[slot] & 8))) {
             double E = 0.0;
             for (int l = lane; l < lane + si.s; ++l) E += P.red[l];
             a.energy[si.g] = float(E);

@@ -17,6 +17,7 @@ int gpolish_group(int mm);
 // Dual Newton polish of every QP (gs lanes each) and the outputs of the solved
 // ones.
 hipError_t launch_newton(int mm, int gs, const KArgs& a, hipStream_t st);
+hipError_t launch_newton_cone(int mm, int gs, const KArgs& a, hipStream_t st);
 // Circular-cone form (KArgs::cone set).
 hipError_t launch_admm_cone(int mm, int occ, const KArgs& a, int grid, size_t lds, hipStream_t st);
 hipError_t launch_finalize_cone(int mm, const KArgs& a, int grid, size_t lds, hipStream_t st);

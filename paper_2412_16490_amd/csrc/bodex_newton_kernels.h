@@ -14,7 +14,7 @@ namespace bodex {
 // the 6 x 6 factor; no LDS beyond the slot table, HBM traffic is the ADMM
 // point in (12 m B per QP) and u out (52 B).
 template <int MM, int GS, bool CONE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 ? 3 : 2))) newton_kernel(const KArgs a) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) newton_kernel(const KArgs a) {
     constexpr int NC = (MM + GS - 1) / GS, PER = kWave / GS;
     using Store = NewtonStore<NC>;
     extern __shared__ __align__(16) double sGeo[];  // [slots MM + 1 (padding)][12]

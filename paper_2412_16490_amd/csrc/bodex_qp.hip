@@ -261,6 +261,16 @@ int ensure_device(bodex_qp* h, void** ptr, size_t* cap, size_t need) {
         drop_graphs(h);
     }
     size_t extra = need - *cap;
+    // the cone's polish workspace makes room (it is set up after every other
+    // allocation of a call, and only where it fits)
+    if (h->owned_bytes + extra > h->budget && h->d_spill && ptr != &h->d_spill &&
+        h->prm.friction_cone == BODEX_CONE_CIRCULAR) {
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        HIP_TRY(h, hipFree(h->d_spill));
+        h->owned_bytes -= h->d_spill_cap;
+        h->d_spill = nullptr;
+        h->d_spill_cap = 0;
+    }
     if (h->owned_bytes + extra > h->budget)
         return fail(h, BODEX_EBUDGET, "workspace of %zu bytes exceeds the budget of %zu bytes",
                     h->owned_bytes + extra, h->budget);
@@ -372,14 +382,22 @@ hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStrea
     return a.cone ? bodex::launch_backward_cone(mm, a, grid, lds, st) : bodex::launch_backward(mm, a, grid, lds, st);
 }
 
-// Dual Newton polish (bodex_newton.h): for the pyramid without the normal-sum
-// row, unless polish_chunk 0 asks for the one-lane kernel.  eps at least
-// 5e-7: the method's forces carry the rounding of |beta t| / eps (1e-16 of 1e6
-// at the default 1e-6); below that the active-set polish, which works in the
-// forces, is the more accurate one.
-bool newton_applies(const bodex_qp_params& p) {
-    return (p.flags & BODEX_F_POLISH) && p.friction_cone == BODEX_CONE_PYRAMID8 && p.gamma == 0.f &&
-           p.polish_chunk != 0 && p.polish_steps > 0 && p.eps_reg >= 5e-7f;
+// Dual Newton polish (bodex_newton.h), without the normal-sum row, unless
+// polish_chunk 0 asks for the one-lane kernels: for the pyramid, and for the
+// circular cone up to kConeNewtonQps QPs.  eps at least 5e-7: the method's
+// forces carry the rounding of |beta t| / eps (1e-16 of 1e6 at the default
+// 1e-6); below that the polishes that work in the forces are the more accurate.
+// The cone's limit is not one of speed (barrier / Newton polish: 384 QPs 1.53 /
+// 0.07 ms, 131,072 QPs 9.0 / 0.5 ms) but of equal results: about two QPs in a
+// million leave the barrier polish 3e-4 to 2e-3 off the minimiser in weakly
+// determined force directions (60 batches of 131,072 QPs, against 64 bits;
+// the Newton polish of the same QPs: 1e-7), so that below the limit a batch
+// sees a difference beyond the force tolerance's scale in one of 60 cases at
+// most, and large batches keep the forces they had.
+constexpr int kConeNewtonQps = 8192;
+bool newton_applies(const bodex_qp_params& p, int n_qps) {
+    return (p.flags & BODEX_F_POLISH) && p.gamma == 0.f && p.polish_chunk != 0 && p.polish_steps > 0 &&
+           p.eps_reg >= 5e-7f && (p.friction_cone == BODEX_CONE_PYRAMID8 || n_qps <= kConeNewtonQps);
 }
 
 // Lanes per QP.  More lanes shorten the chain of a QP's steps, fewer waste
@@ -388,8 +406,11 @@ bool newton_applies(const bodex_qp_params& p) {
 // 32,768 358 / 316 / 320, 131,072 899 / 806 / 688, 262,144 1658 / 1434 / 1142
 // (6 contacts alike); 4 contacts (4 / 2 lanes) 32,766 QPs 256 / 283, 98,304
 // 491 / 471, 262,140 1075 / 930; 8 contacts 16,379 QPs 263 / 266 / 342, 65,527
-// 589 / 525 / 571, 131,065 1011 / 873 / 911.
-int newton_group(int mm, int n_qps) {
+// 589 / 525 / 571, 131,065 1011 / 873 / 911.  The cone (at
+// most kConeNewtonQps QPs): 5 contacts, 1024 QPs 96 / 140 / 174; 4 contacts,
+// 1020 QPs 126 / 124 / 163.
+int newton_group(int mm, bool cone, int n_qps) {
+    if (cone) return mm <= 4 ? 4 : 8;
     if (mm <= 4) return n_qps <= 65536 ? 4 : 2;
     if (n_qps <= 20480) return 8;
     return mm <= 6 && n_qps > 40960 ? 2 : 4;
@@ -402,17 +423,22 @@ int newton_group(int mm, int n_qps) {
 // room) in a; chunked is false where the chunked polish does not apply (no
 // polish, the circular cone, gamma > 0, chunk 0: effective()).
 // The dual Newton polish takes u and a result word per QP from the same
-// workspace (less than the records need).
-int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, bool& chunked, int& grid_g) {
+// workspace (less than the records need); for the cone, which needs none
+// otherwise, only where the budget has room beside `reserve`, the bytes the
+// call allocates after this, and the one-lane barrier polish runs where not.
+int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, size_t reserve, bool& chunked, int& grid_g) {
     const int chunk = effective(h->prm, W).polish_chunk;
+    const bool newton = newton_applies(h->prm, W);
     chunked = chunk > 0;
     grid_g = 0;
-    if (!chunked) return 0;
+    if (!chunked && !newton) return 0;
     const size_t K = size_t(W);
     const size_t nd = size_t(3 * mm + 3) * K, ni = size_t(bodex::kSpInts) * K + size_t(W);
-    const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, nd * sizeof(double) + ni * sizeof(int));
+    const size_t need = chunked ? nd * sizeof(double) + ni * sizeof(int) : K * (6 * sizeof(double) + sizeof(int));
+    if (!chunked && h->owned_bytes - h->d_spill_cap + std::max(need, h->d_spill_cap) + reserve > h->budget) return 0;
+    const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, need);
     if (rc) return rc;
-    if (newton_applies(h->prm)) {
+    if (newton) {
         a.nu = static_cast<double*>(h->d_spill);
         a.ninfo = reinterpret_cast<int*>(a.nu + 6 * K);
         chunked = false;
@@ -437,8 +463,8 @@ int enqueue_finalize(bodex_qp* h, KArgs f, int mm, bool chunked, int* d_queue, i
     f.queue = nullptr;
     if (f.nu) {
         f.nfail = d_queue + 2;
-        const int gs = newton_group(mm, f.W);
-        HIP_TRY(h, bodex::launch_newton(mm, gs, f, h->stream));
+        const int gs = newton_group(mm, f.cone != 0, f.W);
+        HIP_TRY(h, f.cone ? bodex::launch_newton_cone(mm, gs, f, h->stream) : bodex::launch_newton(mm, gs, f, h->stream));
         f.fin_mode = 3;
         HIP_TRY(h, launch(Kind::Fin, mm, f, std::min(grid_f, 1024), lds_f, h->stream));
     } else if (chunked) {
@@ -798,7 +824,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
     bool chunked = false;
     int grid_g = 0;
     const size_t n_ints = desc_ints(G, S, lay);
-    rc = chunk_setup(h, a, W, mm, chunked, grid_g);
+    rc = chunk_setup(h, a, W, mm, n_ints * sizeof(int), chunked, grid_g);
     if (rc) return rc;
 
     const bool timing = (h->prm.flags & BODEX_F_TIMING) != 0;
@@ -1239,7 +1265,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
     const int grid_a = batched ? occupancy_grid(h, per_cu, S.n_tiles) : S.n_tiles;
     bool chunked = false;
     int grid_g = 0;
-    rc = chunk_setup(h, a, W, mm, chunked, grid_g);
+    rc = chunk_setup(h, a, W, mm, n_ints * sizeof(int), chunked, grid_g);
     if (rc) return rc;
 
     // The whole descent for the descriptors at `desc`: loss weights, the
