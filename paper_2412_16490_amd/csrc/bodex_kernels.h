@@ -248,6 +248,93 @@ __device__ bool coop_inverse(bool do_it, int j, int s, T* Lw, O* Inv, T* yv, Ent
     return ok;
 }
 
+// The FP32 inverse, with the wave's 64 lanes dealt one matrix row (then one
+// column of the inverse) each over several slots at once: the row lives in
+// registers and only column k of the factor passes through LDS per step, where
+// coop_inverse walks its packed matrix there entry by entry, one dependent
+// LDS round trip per multiply.  Every entry sees the same operations in the
+// same order: the ADMM state is bit-identical.  Measured, the ADMM kernel's
+// time less its iterations: 5 contacts, 64 / 8192 grasps 45 -> 30 / 61 -> 47
+// us; 8 contacts, 777 grasps 144 -> 96; 3 to 8 contacts, 37 / 20,000 grasps
+// 77 -> 29 / 325 -> 186.  slots: bit k = slot k is to be inverted; L: the slots'
+// packed-lower workspaces, Inv: their packed-upper outputs (strides in
+// floats); entry(slot, i, c).  Returns the slots with a non-positive pivot.
+template <int NV, typename Entry>
+__device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, size_t ldl, float* Inv, size_t ldi,
+                                                 int* sBad, Entry entry) {
+    constexpr int PER = kWave / NV;  // slots per pass
+    const int q = threadIdx.x / NV, i = threadIdx.x % NV;
+    if (threadIdx.x == 0) *sBad = 0;
+    __syncthreads();
+#pragma unroll 1
+    while (slots) {
+        int slot = -1;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int b = slots ? __builtin_ctz(slots) : -1;
+            slots &= slots - (slots ? 1u : 0u);
+            if (q == k) slot = b;
+        }
+        const bool on = slot >= 0;
+        float* L = Lw + size_t(on ? slot : 0) * ldl;
+        float* Li = L + lo_idx(i, 0);
+        float r[NV];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) r[c] = (on && c <= i) ? entry(slot, i, c) : 0.f;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            if (on && i == k) {
+                float d = r[k];
+                if (!(d > 0.f)) {
+                    atomicOr(sBad, 1 << slot);
+                    d = 1.f;
+                }
+                Li[k] = sqrtf(d);
+            }
+            __syncthreads();
+            float l = 0.f;
+            if (on && i > k) {
+                l = r[k] / L[lo_idx(k, k)];
+                Li[k] = l;
+            }
+            __syncthreads();
+            if (on && i > k) {
+#pragma unroll
+                for (int c = k + 1; c < NV; ++c) r[c] -= l * L[lo_idx(c, k)];
+            }
+            BODEX_SPLIT();
+        }
+        __syncthreads();
+        // column i of the inverse: L L^T x = e_i (the forward solve's terms
+        // above row i are exact zeros)
+        if (on) {
+            float y[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) {
+                float acc = (t == i) ? 1.f : 0.f;
+#pragma unroll
+                for (int c = 0; c < t; ++c) acc -= L[lo_idx(t, c)] * y[c];
+                y[t] = acc / L[lo_idx(t, t)];
+                if (t % 3 == 2) BODEX_SPLIT();
+            }
+#pragma unroll
+            for (int t = NV - 1; t >= 0; --t) {
+                float acc = y[t];
+#pragma unroll
+                for (int c = t + 1; c < NV; ++c) acc -= L[lo_idx(c, t)] * y[c];
+                y[t] = acc / L[lo_idx(t, t)];
+                if (t % 3 == 0) BODEX_SPLIT();
+            }
+            float* out = Inv + size_t(slot) * ldi;
+#pragma unroll
+            for (int t = 0; t < NV; ++t)
+                if (t <= i) out[up_idx<NV>(t, i)] = y[t];
+        }
+        __syncthreads();
+    }
+    return unsigned(*sBad);
+}
+
 // ---------------------------------------------------------------------------
 // Dynamic LDS layouts.
 // ---------------------------------------------------------------------------
@@ -311,12 +398,12 @@ __device__ __forceinline__ void write_admm_zy(const KArgs& a, unsigned w, const 
 // if its factorisation failed.
 template <int MM, bool CONE>
 __device__ __forceinline__ int refactor_slots(const KArgs& a, bool mine, int slot, int j, int s, int m,
-                                              float rho, const float* sG, const float* sMuc, double* sLw,
-                                              float* sKi, double* sYv, int* sMisc) {
+                                              float rho, const SlotInfo* sInfo, const float* sRho, const float* sG,
+                                              const float* sMuc, double* sLw, float* sKi, double* sYv, int* sMisc) {
     constexpr int NV = 3 * MM, NKP = Dims<MM>::NKP, NG = 6 * NV;
     const float* Gs = sG + size_t(slot) * NG;
     const float* mucs = sMuc + slot * 8;
-    if (threadIdx.x == 0) sMisc[1] = 0;
+    if (threadIdx.x == 0) sMisc[1] = sMisc[2] = 0;
     __syncthreads();
     bool want64 = false;
     if (mine) {
@@ -349,13 +436,17 @@ __device__ __forceinline__ int refactor_slots(const KArgs& a, bool mine, int slo
             return v;
         });
     }
-    float* Lf = reinterpret_cast<float*>(Lw);
+    if (mine && !want64 && j == 0) atomicOr(&sMisc[2], 1 << slot);
+    __syncthreads();
     const float eps32 = a.eps;
-    float* yf = reinterpret_cast<float*>(sYv) + threadIdx.x;
-    const bool ok32 = coop_inverse<float, NV>(mine && !want64, j, s, Lf, Ki, yf, [&](int i, int c) {
-        return CONE ? cone_kkt_entry<float, NV>(Gs, m, rho, eps32, i, c)
-                    : kkt_entry<float, NV>(Gs, mucs, m, rho, eps32, i, c);
-    });
+    const unsigned bad32 = wave_inverse<NV>(
+        unsigned(sMisc[2]), reinterpret_cast<float*>(sLw), size_t(NKP) * 2, sKi, NKP, &sMisc[3],
+        [&](int sl, int i, int c) {
+            const float* Gq = sG + size_t(sl) * NG;
+            return CONE ? cone_kkt_entry<float, NV>(Gq, sInfo[sl].m, sRho[sl], eps32, i, c)
+                        : kkt_entry<float, NV>(Gq, sMuc + sl * 8, sInfo[sl].m, sRho[sl], eps32, i, c);
+        });
+    const bool ok32 = !((bad32 >> slot) & 1u);
     int r = 0;
     if (mine && want64) r |= 1;
     if (mine && !(ok && ok32)) r |= 2;
@@ -466,8 +557,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) 
         // --- factorisation ------------------------------------------------------
         unsigned char stbits = 0;
         {
-            const int fr = refactor_slots<MM, CONE>(a, act && !bad, act ? slot : 0, j, si.s, m, rho, sG, sMuc,
-                                                    sLw, sKi, sYv, sMisc);
+            const int fr = refactor_slots<MM, CONE>(a, act && !bad, act ? slot : 0, j, si.s, m, rho, sInfo,
+                                                    sRho, sG, sMuc, sLw, sKi, sYv, sMisc);
             if (fr & 1) stbits |= kStFp64;
             if (fr & 2) bad = true;
         }
@@ -569,8 +660,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) 
                 rho = rn;
             }
             {
-                const int fr = refactor_slots<MM, CONE>(a, mine, act ? slot : 0, j, si.s, m, rho, sG, sMuc, sLw,
-                                                        sKi, sYv, sMisc);
+                const int fr = refactor_slots<MM, CONE>(a, mine, act ? slot : 0, j, si.s, m, rho, sInfo, sRho, sG,
+                                                        sMuc, sLw, sKi, sYv, sMisc);
                 if (fr & 1) stbits |= kStFp64;
                 if ((fr & 2) && mine && !done) {
                     done = true;

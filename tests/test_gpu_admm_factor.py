@@ -1,0 +1,22 @@
+"""The ADMM kernel's FP32 factorisation at the edges of its split: 64 lanes take
+the rows of floor(64 / 3m) slots at a time, so tiles with one slot, with one full
+pass, one slot more and the most slots a tile holds, against the FP64 oracle."""
+import pytest
+
+from paper_2412_16490_amd import api
+from paper_2412_16490_amd import workload as wl
+from gpu_common import run_gpu
+from test_gpu_admm_only import _check_admm_only
+
+pytestmark = pytest.mark.gpu
+
+
+# contacts, wrenches (a tile holds min(12, 64 // wrenches) slots), grasps
+@pytest.mark.parametrize("m,s,ng", [(1, 5, 13), (4, 64, 3), (4, 12, 11), (4, 10, 13), (5, 16, 9), (5, 12, 11),
+                                    (5, 5, 25), (6, 21, 7), (6, 16, 9), (7, 21, 7), (7, 16, 9), (8, 32, 5),
+                                    (8, 21, 7), (8, 5, 25)])
+def test_slots_per_pass(m, s, ng):
+    b = wl.uniform_batch(500 + m, ng, m, s)
+    print("ADMM factor: m %d s %d, %d grasps, tol 1e-5" % (m, s, ng), flush=True)
+    gpu = run_gpu(b, tol_rel=1e-5, max_iters=500, flags=api.F_ADAPTIVE_RHO)
+    _check_admm_only(b, gpu, 1e-5, min_converged=0.5)
