@@ -133,7 +133,7 @@ typedef struct {
                           /* gamma = 0.                                       */
     unsigned flags;       /* BODEX_F_*                                        */
     int admm_waves;       /* ADMM kernel register budget as resident waves   */
-                          /* per SIMD: 1, 2, 3 or 4 (0 = library default)     */
+                          /* per SIMD: 1, 2, 3 or 4 (0 = by batch size)        */
     float admm_tol;       /* ADMM stops a QP at this relative KKT residual;   */
                           /* the polish then lifts it to tol_rel (0 = the     */
                           /* friction model's default: 1e-1 for PYRAMID8,     */

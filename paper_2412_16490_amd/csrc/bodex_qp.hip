@@ -327,7 +327,6 @@ int graph_entry(bodex_qp* h, uint64_t key, size_t n_ints, GraphEntry** out) {
 
 enum class Kind { Admm, Fin, Bwd };
 
-constexpr int kDefaultAdmmWaves = 2;
 // polish_chunk -1 (the default): the chunk by batch size.  Measured at 256
 // to 8192 grasps x 16 wrenches (5 contacts): the contact-parallel polish
 // alone (chunk 1) is 2.8x faster than the one-lane polish at 256 grasps,
@@ -375,8 +374,18 @@ Effective effective(const bodex_qp_params& p, int n_qps) {
     return e;
 }
 
+// admm_waves 0.  Up to one tile per SIMD (4 on each of 256 CUs) nothing is gained by a second
+// resident wave, and the kernel with every register (no spills) is the faster;
+// above, a second wave hides the first one's latency.  The results are the
+// same bits.  Measured, us at 1 / 2 / 3 waves: 5 contacts x 16 wrenches, 64
+// tiles 59 / 73 / 76, 1024 69 / 81 / 87, 1280 124 / 83 / 88; 8 contacts x 11,
+// 64 tiles 180 / 191 / 202, 1024 196 / 206 / 245; circular cone 5 x 16, 1024
+// tiles 591 / 701 / 768, 1280 997 / 724 / 769.
+constexpr int kAdmmOneWaveTiles = 1024;
+int default_admm_waves(int n_tiles) { return n_tiles <= kAdmmOneWaveTiles ? 1 : 2; }
+
 hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStream_t st, int occ = 0) {
-    if (k == Kind::Admm) return bodex::launch_admm(mm, occ > 0 ? occ : kDefaultAdmmWaves, a, grid, lds, st);
+    if (k == Kind::Admm) return bodex::launch_admm(mm, occ > 0 ? occ : default_admm_waves(a.n_tiles), a, grid, lds, st);
     if (k == Kind::Fin)
         return a.cone ? bodex::launch_finalize_cone(mm, a, grid, lds, st) : bodex::launch_finalize(mm, a, grid, lds, st);
     return a.cone ? bodex::launch_backward_cone(mm, a, grid, lds, st) : bodex::launch_backward(mm, a, grid, lds, st);

@@ -1,6 +1,7 @@
 """The ADMM kernel's FP32 factorisation at the edges of its split: 64 lanes take
 the rows of floor(64 / 3m) slots at a time, so tiles with one slot, with one full
 pass, one slot more and the most slots a tile holds, against the FP64 oracle."""
+import numpy as np
 import pytest
 
 from paper_2412_16490_amd import api
@@ -20,3 +21,16 @@ def test_slots_per_pass(m, s, ng):
     print("ADMM factor: m %d s %d, %d grasps, tol 1e-5" % (m, s, ng), flush=True)
     gpu = run_gpu(b, tol_rel=1e-5, max_iters=500, flags=api.F_ADAPTIVE_RHO)
     _check_admm_only(b, gpu, 1e-5, min_converged=0.5)
+
+
+# 64 wrenches fill a tile: 1024 tiles (the last batch of the one-wave kernel)
+# and 1025 give the same bits at every register budget
+@pytest.mark.parametrize("ng", [1024, 1025])
+def test_default_waves_on_both_sides_of_the_rule(ng):
+    b = wl.uniform_batch(520, ng, 4, 64)
+    print("ADMM waves: %d tiles" % ng, flush=True)
+    outs = [run_gpu(b, admm_waves=w) for w in (0, 1, 2)]
+    for o in outs[1:]:
+        for k in ("x", "z", "y"):
+            assert np.array_equal(outs[0]["state"][k], o["state"][k]), k
+        assert np.array_equal(outs[0]["iters"], o["iters"])
