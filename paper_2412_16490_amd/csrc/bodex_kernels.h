@@ -55,6 +55,7 @@ struct KArgs {
     const int* tile_start;
     int n_tiles;
     int slots;  // max grasps per tile (sizes the dynamic LDS)
+    int slots64;  // ADMM: slots per pass of the FP64 factorisation (>= 1)
     int* queue; // persistent launch: tile counter (null = one tile per block)
     int W;
     int ms;     // array stride in contacts (m_max of the caller's layout, <= MM)
@@ -177,92 +178,20 @@ __device__ inline void load_slots(const KArgs& a, int t, SlotInfo* info, int& ns
     __syncthreads();
 }
 
-// Cooperative inverse of an SPD NV x NV matrix per slot.  Every lane of the
-// wave calls it (it contains barriers); lanes of slots with do_it set do the
-// work.  Lw: the slot's packed-lower workspace (type T); Inv: the slot's
-// packed-upper output (type O).  entry(i, c) gives the matrix.  Returns false
-// on a lane whose slot hit a non-positive pivot.
-template <typename T, int NV, typename O, typename Entry>
-__device__ bool coop_inverse(bool do_it, int j, int s, T* Lw, O* Inv, T* yv, Entry entry) {
-    // yv: this lane's solve vector in LDS, yv[i * kWave] (lane-interleaved)
-    bool ok = true;
-    if (do_it) {
-#pragma unroll 1
-        for (int i = j; i < NV; i += s)
-#pragma unroll 1
-            for (int c = 0; c <= i; ++c) Lw[lo_idx(i, c)] = entry(i, c);
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int k = 0; k < NV; ++k) {
-        T d = T(1);
-        if (do_it) {
-            d = Lw[lo_idx(k, k)];
-            if (!(d > T(0))) {
-                ok = false;
-                d = T(1);
-            }
-            d = sqrt(d);
-            #pragma unroll 1
-            for (int i = k + 1 + j; i < NV; i += s) Lw[lo_idx(i, k)] /= d;
-        }
-        __syncthreads();
-        if (do_it) {
-            #pragma unroll 1
-            for (int i = k + 1 + j; i < NV; i += s) {
-                const T lik = Lw[lo_idx(i, k)];
-                #pragma unroll 1
-                for (int c = k + 1; c <= i; ++c) Lw[lo_idx(i, c)] -= lik * Lw[lo_idx(c, k)];
-            }
-        }
-        __syncthreads();
-        if (do_it && j == 0) Lw[lo_idx(k, k)] = d;
-    }
-    __syncthreads();
-    if (do_it) {
-        // column col of the inverse: solve L L^T x = e_col (y = L^{-1} e_col
-        // vanishes above col)
-        #pragma unroll 1
-        for (int col = j; col < NV; col += s) {
-            #pragma unroll 1
-            for (int i = 0; i < col; ++i) yv[i * kWave] = T(0);
-            #pragma unroll 1
-            for (int i = col; i < NV; ++i) {
-                T acc = (i == col) ? T(1) : T(0);
-                #pragma unroll 1
-                for (int c = col; c < i; ++c) acc -= Lw[lo_idx(i, c)] * yv[c * kWave];
-                yv[i * kWave] = acc / Lw[lo_idx(i, i)];
-            }
-            #pragma unroll 1
-            for (int i = NV - 1; i >= 0; --i) {
-                T acc = yv[i * kWave];
-                #pragma unroll 1
-                for (int c = i + 1; c < NV; ++c) acc -= Lw[lo_idx(c, i)] * yv[c * kWave];
-                yv[i * kWave] = acc / Lw[lo_idx(i, i)];
-            }
-            #pragma unroll 1
-            for (int i = 0; i <= col; ++i) Inv[up_idx<NV>(i, col)] = O(yv[i * kWave]);
-        }
-    }
-    __syncthreads();
-    return ok;
-}
-
-// The FP32 inverse, with the wave's 64 lanes dealt one matrix row (then one
-// column of the inverse) each over several slots at once: the row lives in
-// registers and only column k of the factor passes through LDS per step, where
-// coop_inverse walks its packed matrix there entry by entry, one dependent
-// LDS round trip per multiply.  Every entry sees the same operations in the
-// same order: the ADMM state is bit-identical.  Measured, the ADMM kernel's
-// time less its iterations: 5 contacts, 64 / 8192 grasps 45 -> 30 / 61 -> 47
-// us; 8 contacts, 777 grasps 144 -> 96; 3 to 8 contacts, 37 / 20,000 grasps
-// 77 -> 29 / 325 -> 186.  slots: bit k = slot k is to be inverted; L: the slots'
-// packed-lower workspaces, Inv: their packed-upper outputs (strides in
-// floats); entry(slot, i, c).  Returns the slots with a non-positive pivot.
+// FP32 inverse of an SPD NV x NV matrix per slot, with the wave's 64 lanes dealt one
+// matrix row (then one column of the inverse) each over several slots at once:
+// the row lives in registers and only column k of the factor passes through
+// LDS per step.  A factor in LDS walked entry by entry costs one dependent LDS
+// round trip per multiply (measured, the ADMM kernel's time less its
+// iterations: 5 contacts, 64 / 8192 grasps 45 -> 30 / 61 -> 47 us; 8 contacts,
+// 777 grasps 144 -> 96; 3 to 8 contacts, 37 / 20,000 grasps 77 -> 29 / 325 ->
+// 186).  slots: bit k = slot k is to be inverted; Lw: packed-lower workspaces
+// of the slots of one pass; Inv: the slots' packed-upper outputs; entry(slot,
+// i, c).  Returns the slots with a non-positive pivot.  Barriers inside.
 template <int NV, typename Entry>
-__device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, size_t ldl, float* Inv, size_t ldi,
-                                                 int* sBad, Entry entry) {
+__device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, float* Inv, int* sBad, Entry entry) {
     constexpr int PER = kWave / NV;  // slots per pass
+    constexpr int NKP = Dims<NV / 3>::NKP;
     const int q = threadIdx.x / NV, i = threadIdx.x % NV;
     if (threadIdx.x == 0) *sBad = 0;
     __syncthreads();
@@ -276,7 +205,7 @@ __device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, size
             if (q == k) slot = b;
         }
         const bool on = slot >= 0;
-        float* L = Lw + size_t(on ? slot : 0) * ldl;
+        float* L = Lw + size_t(on ? q : 0) * NKP;
         float* Li = L + lo_idx(i, 0);
         float r[NV];
 #pragma unroll
@@ -325,10 +254,96 @@ __device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, size
                 y[t] = acc / L[lo_idx(t, t)];
                 if (t % 3 == 0) BODEX_SPLIT();
             }
-            float* out = Inv + size_t(slot) * ldi;
+            float* out = Inv + size_t(slot) * NKP;
 #pragma unroll
             for (int t = 0; t < NV; ++t)
                 if (t <= i) out[up_idx<NV>(t, i)] = y[t];
+        }
+        __syncthreads();
+    }
+    return unsigned(*sBad);
+}
+
+// The same in FP64, for the slots whose conditioning bound asks for it, with the
+// matrix in LDS, rolled: unrolled like the FP32 form its registers cost the
+// whole kernel 59 -> 72 us (5 contacts x 64 tiles).  per slots at a time, each on
+// lanes64(per) lanes, with NKP + lanes64 * NV doubles of ws.
+template <int NV>
+__host__ __device__ constexpr int lanes64(int per) {
+    return kWave / per < NV ? kWave / per : NV;
+}
+template <int NV, typename Entry>
+__device__ __forceinline__ unsigned wave_inverse64(unsigned slots, int per, double* ws, float* Inv, int* sBad,
+                                                   Entry entry) {
+    constexpr int NKP = Dims<NV / 3>::NKP;
+    const int ln = lanes64<NV>(per), q = threadIdx.x / ln, j = threadIdx.x % ln;
+    const int ys = per * ln;
+    double* L = ws + (q < per ? q : 0) * NKP;
+    double* y = ws + per * NKP + threadIdx.x;  // y[t * ys]: this lane's column, interleaved
+    if (threadIdx.x == 0) *sBad = 0;
+    __syncthreads();
+#pragma unroll 1
+    while (slots) {
+        int slot = -1;
+#pragma unroll 1
+        for (int k = 0; k < per && slots; ++k, slots &= slots - 1)
+            if (q == k) slot = __builtin_ctz(slots);
+        const bool on = slot >= 0;
+        if (on)
+#pragma unroll 1
+            for (int i = j; i < NV; i += ln)
+#pragma unroll 1
+                for (int c = 0; c <= i; ++c) L[lo_idx(i, c)] = entry(slot, i, c);
+        __syncthreads();
+#pragma unroll 1
+        for (int k = 0; k < NV; ++k) {
+            double d = 1.0;
+            if (on) {
+                d = L[lo_idx(k, k)];
+                if (!(d > 0.0)) {
+                    if (j == 0) atomicOr(sBad, 1 << slot);
+                    d = 1.0;
+                }
+                d = sqrt(d);
+#pragma unroll 1
+                for (int i = k + 1 + j; i < NV; i += ln) L[lo_idx(i, k)] /= d;
+            }
+            __syncthreads();
+            if (on) {
+#pragma unroll 1
+                for (int i = k + 1 + j; i < NV; i += ln) {
+                    BODEX_SPLIT();
+                    const double lik = L[lo_idx(i, k)];
+#pragma unroll 1
+                    for (int c = k + 1; c <= i; ++c) L[lo_idx(i, c)] -= lik * L[lo_idx(c, k)];
+                }
+            }
+            if (on && j == 0) L[lo_idx(k, k)] = d;
+            __syncthreads();
+        }
+        if (on) {
+#pragma unroll 1
+            for (int col = j; col < NV; col += ln) {
+                BODEX_SPLIT();
+#pragma unroll 1
+                for (int t = 0; t < col; ++t) y[t * ys] = 0.0;
+#pragma unroll 1
+                for (int t = col; t < NV; ++t) {
+                    double acc = (t == col) ? 1.0 : 0.0;
+#pragma unroll 1
+                    for (int c = col; c < t; ++c) acc -= L[lo_idx(t, c)] * y[c * ys];
+                    y[t * ys] = acc / L[lo_idx(t, t)];
+                }
+#pragma unroll 1
+                for (int t = NV - 1; t >= 0; --t) {
+                    double acc = y[t * ys];
+#pragma unroll 1
+                    for (int c = t + 1; c < NV; ++c) acc -= L[lo_idx(c, t)] * y[c * ys];
+                    y[t * ys] = acc / L[lo_idx(t, t)];
+                }
+#pragma unroll 1
+                for (int t = 0; t <= col; ++t) Inv[size_t(slot) * NKP + up_idx<NV>(t, col)] = float(y[t * ys]);
+            }
         }
         __syncthreads();
     }
@@ -341,9 +356,22 @@ __device__ __forceinline__ unsigned wave_inverse(unsigned slots, float* Lw, size
 template <int MM>
 struct AdmmLds {
     static constexpr int NV = 3 * MM, NK = NV * (NV + 1) / 2, NKP = Dims<MM>::NKP, NG = 6 * NV;
-    static __host__ __device__ size_t bytes(int slots) {
-        return size_t(slots) * (NKP * 4 + NG * 4 + 8 * 4 + NKP * 8) + size_t(64) * NV * 8 +
-               size_t(64) * NV * 4 + 64 * 8 + kMaxSlots * 32 + 64;
+    // Factorisation workspace in doubles: slots64 slots in FP64, or one pass of
+    // FP32 (which always fits), not one matrix per slot of the tile: the LDS of a
+    // tile sets how many are resident (measured, us, ADMM kernel: 8
+    // contacts x 11 wrenches, 1280 tiles 400 -> 206; 6 x 11, 1536 tiles 220 ->
+    // 123; 4 x 6, 2048 tiles 140 -> 84).
+    static __host__ __device__ int ws(int slots64) { return (slots64 * (NKP + lanes64<NV>(slots64) * NV) + 1) & ~1; }
+    static_assert((NKP + NV * NV) * 8 >= (kWave / NV) * NKP * 4, "the FP32 pass must fit");  // ws rises with slots64
+    static __host__ __device__ size_t bytes(int slots, int slots64) {
+        return size_t(slots) * (NKP * 4 + NG * 4 + 8 * 4) + size_t(ws(slots64)) * 8 + size_t(64) * NV * 4 + 64 * 8 +
+               kMaxSlots * 32 + 64;
+    }
+    // The most FP64 slots per pass that leave a tile `budget` bytes, at least one.
+    static int fit64(int slots, size_t budget) {
+        int k = slots;
+        while (k > 1 && bytes(slots, k) > budget) --k;
+        return std::max(k, 1);
     }
 };
 
@@ -397,31 +425,30 @@ __device__ __forceinline__ void write_admm_zy(const KArgs& a, unsigned w, const 
 // wave (barriers inside).  Returns bit 1 if this lane's slot used FP64, bit 2
 // if its factorisation failed.
 template <int MM, bool CONE>
-__device__ __forceinline__ int refactor_slots(const KArgs& a, bool mine, int slot, int j, int s, int m,
-                                              float rho, const SlotInfo* sInfo, const float* sRho, const float* sG,
-                                              const float* sMuc, double* sLw, float* sKi, double* sYv, int* sMisc) {
-    constexpr int NV = 3 * MM, NKP = Dims<MM>::NKP, NG = 6 * NV;
-    const float* Gs = sG + size_t(slot) * NG;
-    const float* mucs = sMuc + slot * 8;
+__device__ __forceinline__ int refactor_slots(const KArgs& a, bool mine, int slot, int j, int m, float rho,
+                                              const SlotInfo* sInfo, const float* sRho, const float* sG,
+                                              const float* sMuc, double* sLw, float* sKi, int* sMisc) {
+    constexpr int NV = 3 * MM, NG = 6 * NV;
     if (threadIdx.x == 0) sMisc[1] = sMisc[2] = 0;
     __syncthreads();
     bool want64 = false;
     if (mine) {
+        const float* Gs = sG + size_t(slot) * NG;
         const float cb = CONE ? cone_kkt_cond_bound<float, NV>(Gs, m, rho, a.eps)
-                              : kkt_cond_bound<float, NV>(Gs, mucs, m, rho, a.eps);
+                              : kkt_cond_bound<float, NV>(Gs, sMuc + slot * 8, m, rho, a.eps);
         want64 = !(cb <= a.fp64_cond);
-        if (want64) atomicOr(&sMisc[1], 1);
+        if (j == 0) atomicOr(&sMisc[want64 ? 1 : 2], 1 << slot);
     }
     __syncthreads();
-    const bool any64 = sMisc[1] != 0;
-    double* Lw = sLw + size_t(slot) * NKP;
-    float* Ki = sKi + size_t(slot) * NKP;
-    bool ok = true;
-    if (any64) {
-        const double rr = double(rho), eps = double(a.eps);
-        ok = coop_inverse<double, NV>(mine && want64, j, s, Lw, Ki, sYv + threadIdx.x, [&](int i, int c) {
-            const int ci = i / 3, cj = c / 3;
-            if (ci >= m || cj >= m) return (i == c) ? 1.0 : 0.0;
+    const unsigned slots64 = __builtin_amdgcn_readfirstlane(sMisc[1]), slots32 = __builtin_amdgcn_readfirstlane(sMisc[2]);
+    unsigned bad = 0;
+    if (__builtin_expect(slots64 != 0, 0)) {
+        const double eps = double(a.eps);
+        bad = wave_inverse64<NV>(slots64, a.slots64, sLw, sKi, &sMisc[3], [&](int k, int i, int c) {
+            const float *Gs = sG + size_t(k) * NG, *mucs = sMuc + k * 8;
+            const int ci = i / 3, cj = c / 3, mk = sInfo[k].m;
+            const double rr = double(sRho[k]);
+            if (ci >= mk || cj >= mk) return (i == c) ? 1.0 : 0.0;
             double sacc = 0.0;
             for (int r = 0; r < 6; ++r) sacc += double(Gs[r * NV + i]) * double(Gs[r * NV + c]);
             double v = 2.0 * sacc + ((i == c) ? 2.0 * eps : 0.0);
@@ -435,21 +462,19 @@ __device__ __forceinline__ int refactor_slots(const KArgs& a, bool mine, int slo
             }
             return v;
         });
+        __syncthreads();
     }
-    if (mine && !want64 && j == 0) atomicOr(&sMisc[2], 1 << slot);
-    __syncthreads();
-    const float eps32 = a.eps;
-    const unsigned bad32 = wave_inverse<NV>(
-        unsigned(sMisc[2]), reinterpret_cast<float*>(sLw), size_t(NKP) * 2, sKi, NKP, &sMisc[3],
-        [&](int sl, int i, int c) {
-            const float* Gq = sG + size_t(sl) * NG;
-            return CONE ? cone_kkt_entry<float, NV>(Gq, sInfo[sl].m, sRho[sl], eps32, i, c)
-                        : kkt_entry<float, NV>(Gq, sMuc + sl * 8, sInfo[sl].m, sRho[sl], eps32, i, c);
+    if (slots32) {
+        const float eps32 = a.eps;
+        bad |= wave_inverse<NV>(slots32, reinterpret_cast<float*>(sLw), sKi, &sMisc[3], [&](int k, int i, int c) {
+            const float* Gs = sG + size_t(k) * NG;
+            return CONE ? cone_kkt_entry<float, NV>(Gs, sInfo[k].m, sRho[k], eps32, i, c)
+                        : kkt_entry<float, NV>(Gs, sMuc + k * 8, sInfo[k].m, sRho[k], eps32, i, c);
         });
-    const bool ok32 = !((bad32 >> slot) & 1u);
+    }
     int r = 0;
     if (mine && want64) r |= 1;
-    if (mine && !(ok && ok32)) r |= 2;
+    if (mine && ((bad >> slot) & 1u)) r |= 2;
     return r;
 }
 
@@ -466,9 +491,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) 
     extern __shared__ __align__(16) unsigned char smem[];
     const int S = a.slots;
     // carve: Lw (double) first for alignment
-    double* sLw = reinterpret_cast<double*>(smem);                       // [S][NKP]
-    double* sYv = sLw + size_t(S) * NKP;                                  // [NV][64]
-    float* sKi = reinterpret_cast<float*>(sYv + size_t(NV) * kWave);     // [S][NKP]
+    double* sLw = reinterpret_cast<double*>(smem);                       // factorisation
+    float* sKi = reinterpret_cast<float*>(sLw + AdmmLds<MM>::ws(a.slots64));  // [S][NKP]
     float* sBq = sKi + size_t(S) * NKP;                                   // [NV][64]
     float* sG = sBq + size_t(NV) * kWave;                                 // [S][NG]
     float* sMuc = sG + size_t(S) * NG;                                    // [S][8]
@@ -557,8 +581,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) 
         // --- factorisation ------------------------------------------------------
         unsigned char stbits = 0;
         {
-            const int fr = refactor_slots<MM, CONE>(a, act && !bad, act ? slot : 0, j, si.s, m, rho, sInfo,
-                                                    sRho, sG, sMuc, sLw, sKi, sYv, sMisc);
+            const int fr = refactor_slots<MM, CONE>(a, act && !bad, act ? slot : 0, j, m, rho, sInfo, sRho,
+                                                    sG, sMuc, sLw, sKi, sMisc);
             if (fr & 1) stbits |= kStFp64;
             if (fr & 2) bad = true;
         }
@@ -660,8 +684,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) 
                 rho = rn;
             }
             {
-                const int fr = refactor_slots<MM, CONE>(a, mine, act ? slot : 0, j, si.s, m, rho, sInfo, sRho, sG,
-                                                        sMuc, sLw, sKi, sYv, sMisc);
+                const int fr = refactor_slots<MM, CONE>(a, mine, act ? slot : 0, j, m, rho, sInfo, sRho, sG,
+                                                        sMuc, sLw, sKi, sMisc);
                 if (fr & 1) stbits |= kStFp64;
                 if ((fr & 2) && mine && !done) {
                     done = true;

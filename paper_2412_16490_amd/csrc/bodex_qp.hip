@@ -149,13 +149,32 @@ int kernel_mm(int m_max) {
     return 0;
 }
 
-size_t admm_lds(int mm, int slots) {
+// One tile per SIMD (4 on each of 256 CUs): up to here a launch of the ADMM
+// kernel gains nothing from a second resident wave.
+constexpr int kAdmmOneWaveTiles = 1024;
+
+// LDS bytes of an ADMM tile; sets a.slots64.  The FP64 factorisation takes as
+// many slots at a time as fit the share of the 160 KB that the launch's
+// residency leaves a tile: a quarter, or an eighth when two waves per SIMD run
+// and fp64_cond is at least its default, with which slots in FP64 are rare.
+// With FP64 forced on every slot (fp64_cond 1) an eighth is the slower: 8
+// contacts x 11 wrenches, 8192 grasps 458 us at a quarter, 820 at an eighth; in
+// FP32 415 at a quarter, 381 at an eighth.
+constexpr float kFp64Cond = 1e4f;
+template <int MM>
+size_t admm_lds_mm(bodex::KArgs& a, int slots, int n_tiles) {
+    using L = bodex::AdmmLds<MM>;
+    const bool quarter = n_tiles <= kAdmmOneWaveTiles || !(a.fp64_cond >= kFp64Cond);
+    a.slots64 = L::fit64(slots, size_t(160 * 1024) / (quarter ? 4 : 8));
+    return L::bytes(slots, a.slots64);
+}
+size_t admm_lds(int mm, bodex::KArgs& a, int slots, int n_tiles) {
     switch (mm) {
-        case 4: return bodex::AdmmLds<4>::bytes(slots);
-        case 5: return bodex::AdmmLds<5>::bytes(slots);
-        case 6: return bodex::AdmmLds<6>::bytes(slots);
-        case 7: return bodex::AdmmLds<7>::bytes(slots);
-        case 8: return bodex::AdmmLds<8>::bytes(slots);
+        case 4: return admm_lds_mm<4>(a, slots, n_tiles);
+        case 5: return admm_lds_mm<5>(a, slots, n_tiles);
+        case 6: return admm_lds_mm<6>(a, slots, n_tiles);
+        case 7: return admm_lds_mm<7>(a, slots, n_tiles);
+        case 8: return admm_lds_mm<8>(a, slots, n_tiles);
     }
     return 0;
 }
@@ -381,7 +400,6 @@ Effective effective(const bodex_qp_params& p, int n_qps) {
 // tiles 59 / 73 / 76, 1024 69 / 81 / 87, 1280 124 / 83 / 88; 8 contacts x 11,
 // 64 tiles 180 / 191 / 202, 1024 196 / 206 / 245; circular cone 5 x 16, 1024
 // tiles 591 / 701 / 768, 1280 997 / 724 / 769.
-constexpr int kAdmmOneWaveTiles = 1024;
 int default_admm_waves(int n_tiles) { return n_tiles <= kAdmmOneWaveTiles ? 1 : 2; }
 
 hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStream_t st, int occ = 0) {
@@ -713,7 +731,7 @@ void bodex_qp_default_params(bodex_qp_params* p) {
     p->rho_min = 1e-4f;
     p->rho_max = 1e4f;
     p->rho_hysteresis = 5.0f;
-    p->fp64_cond = 1e4f;
+    p->fp64_cond = kFp64Cond;
     p->polish_steps = 128;
     p->polish_chunk = kDefaultPolishChunk;
     p->flags = BODEX_F_POLISH | BODEX_F_ADAPTIVE_RHO;
@@ -838,7 +856,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
 
     const bool timing = (h->prm.flags & BODEX_F_TIMING) != 0;
     const bool graph = (h->prm.flags & BODEX_F_GRAPH) != 0 && h->stream != nullptr;
-    const size_t lds_a = admm_lds(mm, S.slots);
+    const size_t lds_a = admm_lds(mm, a, S.slots, S.n_tiles);
     const size_t lds_f = cone ? bodex::cone_fin_lds(mm, S.slots, h->prm.gamma > 0.f) : fin_lds(mm, S.slots, false);
     int per_cu = std::max(1, std::min(16, int((160 * 1024) / std::max<size_t>(lds_a, 1))));
     const int grid_a = batched ? occupancy_grid(h, per_cu, S.n_tiles) : S.n_tiles;
@@ -1013,7 +1031,7 @@ int bodex_qp_solve_static(bodex_qp_t* h, const bodex_batch* in, bodex_result* ou
     a.n_tiles = n_tiles;
     a.slots = slots;
     a.queue = nullptr;
-    const size_t lds_a = admm_lds(mm, slots);
+    const size_t lds_a = admm_lds(mm, a, slots, n_tiles);
     const size_t lds_f = cone ? bodex::cone_fin_lds(mm, slots, h->prm.gamma > 0.f) : fin_lds(mm, slots, false);
     HIP_TRY(h, launch(Kind::Admm, mm, a, n_tiles, lds_a, h->stream, h->prm.admm_waves));
     HIP_TRY(h, launch(Kind::Fin, mm, a, n_tiles, lds_f, h->stream));
@@ -1267,7 +1285,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
     a.status = out->status;
     a.pflops = out->polish_flops;
     const size_t n_ints = desc_ints(G, S, false);
-    const size_t lds_a = admm_lds(mm, S.slots);
+    const size_t lds_a = admm_lds(mm, a, S.slots, S.n_tiles);
     const size_t lds_f = cone ? bodex::cone_fin_lds(mm, S.slots, h->prm.gamma > 0.f) : fin_lds(mm, S.slots, false);
     const size_t lds_b = fin_lds(mm, S.slots, true);
     const int per_cu = std::max(1, std::min(16, int((160 * 1024) / std::max<size_t>(lds_a, 1))));

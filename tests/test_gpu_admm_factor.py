@@ -4,9 +4,10 @@ pass, one slot more and the most slots a tile holds, against the FP64 oracle."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2412_16490_amd import api
 from paper_2412_16490_amd import workload as wl
-from gpu_common import run_gpu
+from gpu_common import check_forward, oracle_params, run_gpu
 from test_gpu_admm_only import _check_admm_only
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +35,23 @@ def test_default_waves_on_both_sides_of_the_rule(ng):
         for k in ("x", "z", "y"):
             assert np.array_equal(outs[0]["state"][k], o["state"][k]), k
         assert np.array_equal(outs[0]["iters"], o["iters"])
+
+
+# FP64 on every grasp: as many slots per pass as fit, at tiles of 1, 2, 5 and
+# 12 slots, below and above the size at which the workspace is halved
+@pytest.mark.parametrize("m,s,ng", [(4, 10, 13), (5, 64, 3), (8, 32, 5), (8, 11, 11), (8, 5, 25), (8, 64, 1030)])
+def test_fp64_slots_per_pass(m, s, ng):
+    b = wl.uniform_batch(540 + m, ng, m, s)
+    print("ADMM FP64 factor: m %d s %d, %d grasps" % (m, s, ng), flush=True)
+    every = range(0, ng, max(1, ng // 25))
+    sub = b.subset(list(every))
+    ref = oracle.solve_batch(sub.counts, sub.woff, sub.points, sub.normals, sub.mu, sub.wrench, prm=oracle_params())
+    check_forward(sub, run_gpu(sub, fp64_cond=1.0), ref)
+    # ADMM alone (the polish splits its sums by batch size): the grasps give the
+    # same bits in the whole batch and in the part
+    full = run_gpu(b, fp64_cond=1.0, flags=api.F_ADAPTIVE_RHO)
+    part = run_gpu(sub, fp64_cond=1.0, flags=api.F_ADAPTIVE_RHO)
+    assert np.all(full["status"] & api.ST_FP64_CHOL) and np.all(part["status"] & api.ST_FP64_CHOL)
+    cols = np.concatenate([np.arange(b.woff[g], b.woff[g + 1]) for g in every])
+    for k in ("x", "z", "y"):
+        assert np.array_equal(full["state"][k][:, cols], part["state"][k]), k
