@@ -189,7 +189,7 @@ def main():
     kernels = {
         "admm": {"bound": "alu", "kernel": "admm_kernel<5>", "dtype": "f32", "peak": PEAK_FP32_TFLOPS,
                  "ms": admm_avg, "flops": flops_a},
-        "finalize": {"bound": "alu", "kernel": "FP64 polish: finalize_kernel<5> passes + gpolish_kernel<5,8>",
+        "finalize": {"bound": "alu", "kernel": "FP64 polish: newton_kernel<5,2> + newton_out_kernel<5>",
                      "dtype": "f64", "peak": PEAK_FP64_TFLOPS, "ms": fin_avg, "flops": flops_f},
     }
 

@@ -121,14 +121,12 @@ typedef struct {
                           /* the pyramid with gamma = 0 and eps_reg >= 5e-7   */
                           /* takes the dual Newton polish.  Where that does   */
                           /* not apply: factorisations a QP takes in the      */
-                          /* one-lane FP64                                    */
-                          /* polish before it is handed to the contact-       */
-                          /* parallel polish (a group of lanes, one per       */
-                          /* contact); 0 = every polish ends in the one-lane  */
-                          /* kernel; -1 = chosen by the number of QPs (1 up   */
-                          /* to 40,960, else 16).  A QP is                    */
-                          /* also handed on at its next factorisation once at */
-                          /* most 8 lanes of its wavefront still polish.      */
+                          /* one-lane FP64 polish before it is handed to the  */
+                          /* contact-parallel polish (a group of lanes, one   */
+                          /* per contact); -1 = chosen by the number of QPs   */
+                          /* (1 up to 40,960, else 16).  A QP is also handed  */
+                          /* on at its next factorisation once at most 8      */
+                          /* lanes of its wavefront still polish.             */
                           /* Used with BODEX_F_POLISH, the pyramid and        */
                           /* gamma = 0.                                       */
     unsigned flags;       /* BODEX_F_*                                        */

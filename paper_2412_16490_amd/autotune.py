@@ -8,7 +8,8 @@ knobs and keeps the fastest configuration whose results are all converged:
                    shape: one lane per QP, 64 QPs per wavefront) before it is
                    handed to the contact-parallel polish (group shape: one
                    lane per contact, 8 or 16 QPs per wavefront); 0 keeps every
-                   QP in the one-lane polish, 1 hands nearly all on;
+                   QP in the one-lane polish, 1 hands nearly all on.  Where
+                   the dual Newton polish applies, every value but 0 takes it;
 * ``admm_waves``   register budget of the ADMM kernel as resident waves per
                    SIMD (1 = no cap, 2, 3, 4): trades spills for occupancy;
 * ``check_every``  iterations between residual checks / rho updates;

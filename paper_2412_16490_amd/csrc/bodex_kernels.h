@@ -12,8 +12,12 @@
 //   admm_kernel      grasp matrix, per-grasp factorisation, fused ADMM loop with
 //                    periodic residual checks and per-grasp rho adaptation;
 //                    writes the state (x, z, y, rho), iterations and status.
+//   newton_kernel    (bodex_newton_kernels.h) FP64 polish of the pyramid without
+//                    the normal-sum row, and of small cone batches; its outputs
+//                    from newton_out_kernel.
 //   finalize_kernel  FP64 polish (reduced KKT re-solve with dual active-set
-//                    correction), objective, energy, KKT residual, outputs.
+//                    correction) of the rest and of what Newton leaves,
+//                    objective, energy, KKT residual, outputs.
 //   backward_kernel  recomputes f* from the state, Danskin gradient of the
 //                    energy with respect to G, chain rule to points/normals.
 #pragma once

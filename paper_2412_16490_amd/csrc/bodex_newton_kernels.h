@@ -11,8 +11,13 @@ namespace bodex {
 // Solve: GS lanes per QP, 64 / GS QPs per one-wave workgroup; the GS parts of
 // a tile are separate workgroups, so a hard QP holds up no more than the
 // other groups of its wave.  Bound by FP64 issue and the dependent chain of
-// the 6 x 6 factor; no LDS beyond the slot table, HBM traffic is the ADMM
-// point in (12 m B per QP) and u out (52 B).
+// the 6 x 6 factor and of the slopes; HBM traffic is the ADMM point in (12 m B
+// per QP) and u out (52 B).  The contacts' geometry, the proximal centre and the
+// group's scalars are in LDS: an early form with everything in registers (256,
+// and spills) took 1105 us at 5 contacts and 131,072 QPs, with these in LDS 862
+// (8 lanes per QP) and 734 (2 lanes).  At 629 us now (2 lanes), it and
+// newton_out_kernel (44 us) replace, for the pyramid, the one-lane and
+// contact-parallel active-set passes (1157 + 466 + 58 us).
 template <int MM, int GS, bool CONE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) newton_kernel(const KArgs a) {
     constexpr int NC = (MM + GS - 1) / GS, PER = kWave / GS;

@@ -346,7 +346,8 @@ int graph_entry(bodex_qp* h, uint64_t key, size_t n_ints, GraphEntry** out) {
 
 enum class Kind { Admm, Fin, Bwd };
 
-// polish_chunk -1 (the default): the chunk by batch size.  Measured at 256
+// polish_chunk -1 (the default): the chunk by batch size, where the active-set
+// polish runs (see newton_applies).  Measured at 256
 // to 8192 grasps x 16 wrenches (5 contacts): the contact-parallel polish
 // alone (chunk 1) is 2.8x faster than the one-lane polish at 256 grasps,
 // 1.9x at 1024 and 1.4x at 2048, where its latency wins; from 4096 grasps
@@ -357,7 +358,7 @@ enum class Kind { Admm, Fin, Bwd };
 constexpr int kDefaultPolishChunk = -1;
 int auto_polish_chunk(int n_qps) { return n_qps <= 40960 ? 1 : 16; }
 // ADMM stopping rule with the polish on, per friction model (admm_tol 0).
-// The pyramid's active-set polish costs the same from a rough point: 1e-1.
+// The pyramid's polish costs about the same from a rough point: 1e-1.
 // The cone's barrier polish is faster from a closer one (headline batch:
 // finalize 19.7 ms from 1e-2, 12.5 ms from 1e-4 or tighter); the few QPs
 // that take hundreds of iterations to get there hold up their whole grasp,
@@ -367,8 +368,8 @@ constexpr float kAdmmTolPyramid = 1e-1f, kAdmmTolCone = 1e-4f;
 constexpr int kAdmmItersCone = 200;
 // The pyramid's ADMM under that rule is only a warm start, checked first
 // after 20 iterations rather than 10: the polish from the 20-iteration point
-// is faster by more than the extra iterations cost (headline batch, ADMM +
-// polish: 1.87-1.90 ms against 1.95-1.99 ms).
+// is faster by more than the extra iterations cost (5 contacts x 16 wrenches,
+// 8192 grasps, whole solve: 0.79 ms against 0.84).
 constexpr int kAdmmCheckPyramid = 20;
 
 // The rules the parameters leave to the library: ADMM's stopping

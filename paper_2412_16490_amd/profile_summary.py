@@ -33,8 +33,9 @@ CSRC = os.path.join(HERE, "csrc")
 # figure is reported only while these files are unchanged.
 KERNEL_FILES = {
     "admm": ("bodex_math.h", "bodex_cone.h", "bodex_kernels.h", "k_admm.hip", "bodex_qp.hip"),
-    "finalize": ("bodex_math.h", "bodex_cone.h", "bodex_gpolish.h", "bodex_kernels.h", "k_finalize.hip",
-                 "k_finalize_sum.hip", "k_finalize_chunk.hip", "k_gpolish.hip", "bodex_qp.hip"),
+    "finalize": ("bodex_math.h", "bodex_cone.h", "bodex_gpolish.h", "bodex_kernels.h", "bodex_newton.h",
+                 "bodex_newton_kernels.h", "k_newton.hip", "k_finalize.hip", "k_finalize_sum.hip",
+                 "k_finalize_chunk.hip", "k_gpolish.hip", "bodex_qp.hip"),
     "cone_finalize": ("bodex_math.h", "bodex_cone.h", "bodex_kernels.h", "k_finalize_cone.hip", "bodex_qp.hip"),
     "detach": ("bodex_launch.h", "k_detach.hip"),
 }
