@@ -864,12 +864,13 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
     // finalize: one block per tile (the polish keeps its state in registers)
     const int grid_f = S.n_tiles;
 
-    // Enqueue the launch sequence (reset counters, ADMM, finalize) for the
-    // descriptors at d.
-    auto enqueue = [&](int* d, bool with_events) -> int {
+    // Enqueue the launch sequence (ADMM, finalize) for the descriptors at d, in
+    // a captured graph after a reset of the counters; a direct call's upload
+    // zeroes them (the reset's launch: 2 to 5 us of a 200 us solve).
+    auto enqueue = [&](int* d, bool with_events, bool reset) -> int {
         bind_desc(a, d, G, S, lay);
         int* d_queue = d + (n_ints - 4);
-        HIP_TRY(h, bodex::launch_reset(d_queue, 4, h->stream));
+        if (reset) HIP_TRY(h, bodex::launch_reset(d_queue, 4, h->stream));
         KArgs aa = a;
         aa.queue = batched ? d_queue : nullptr;
         if (with_events) HIP_TRY(h, hipEventRecord(h->tev[0], h->stream));
@@ -895,9 +896,9 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
         size_t up = 0;
         rc = upload_desc(h, in, S, h->d_desc, &up, lay ? &st : nullptr);
         if (rc) return rc;
-        rc = enqueue(h->d_desc, timing);
+        rc = enqueue(h->d_desc, timing, false);
         if (rc) return rc;
-        h->last_launches = (a.nu || chunked) ? 5 : 3;
+        h->last_launches = (a.nu || chunked) ? 4 : 2;
         h->t_admm = h->t_fin = timing;
         return 0;
     }
@@ -922,7 +923,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
         if (rc) return rc;
         hipGraph_t gr = nullptr;
         HIP_TRY(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-        rc = enqueue(hit->d_desc, false);
+        rc = enqueue(hit->d_desc, false, true);
         hipError_t ce = hipStreamEndCapture(h->stream, &gr);
         if (rc) return rc;
         if (ce != hipSuccess) return hip_fail(h, ce, "hipStreamEndCapture");
@@ -1297,9 +1298,10 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
     if (rc) return rc;
 
     // The whole descent for the descriptors at `desc`: loss weights, the
-    // first contacts, then per step reset, ADMM, finalize, backward and the
-    // pose step (which re-queries the contacts of the new pose).
-    auto enqueue = [&](int* desc) -> int {
+    // first contacts, then per step ADMM, finalize, backward and the pose step
+    // (which re-queries the contacts of the new pose and zeroes the counters for
+    // the next step).
+    auto enqueue = [&](int* desc, bool reset) -> int {
         KArgs ad = a;
         bind_desc(ad, desc, G, S);
         int* d_queue = desc + (n_ints - 4);
@@ -1308,12 +1310,12 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
         ha.points = P;
         ha.normals = N;
         ha.dist = D;
+        if (reset) HIP_TRY(h, bodex::launch_reset(d_queue, 4, h->stream));
         HIP_TRY(h, bodex::launch_fill(wq, G, d->w_qp, h->stream));
         HIP_TRY(h, bodex::launch_hand_query(ha, h->stream));
         for (int k = 0; k < d->iters; ++k) {
             KArgs ak = ad;
             if (k > 0) ak.warm = 1;
-            HIP_TRY(h, bodex::launch_reset(d_queue, 4, h->stream));
             ak.queue = batched ? d_queue : nullptr;
             HIP_TRY(h, launch(Kind::Admm, mm, ak, grid_a, lds_a, h->stream, h->prm.admm_waves));
             const int rf = enqueue_finalize(h, ak, mm, chunked, d_queue, S.n_tiles, grid_g, lds_f);
@@ -1339,6 +1341,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
             hs.step_rot = d->step_rot;
             hs.step_trans = d->step_trans;
             hs.requery = 1;
+            hs.clear = d_queue;
             HIP_TRY(h, bodex::launch_hand_step(hs, h->stream));
         }
         return 0;
@@ -1352,9 +1355,9 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
         size_t up = 0;
         rc = upload_desc(h, &qb, S, h->d_desc, &up);
         if (rc) return rc;
-        rc = enqueue(h->d_desc);
+        rc = enqueue(h->d_desc, false);
         if (rc) return rc;
-        h->last_launches = 2 + ((a.nu || chunked) ? 7 : 5) * d->iters;
+        h->last_launches = 2 + ((a.nu || chunked) ? 6 : 4) * d->iters;
         return 0;
     }
     // Graph path: the descent's launches captured once per shape, pointers
@@ -1378,7 +1381,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
         if (rc) return rc;
         hipGraph_t gr = nullptr;
         HIP_TRY(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-        rc = enqueue(hit->d_desc);
+        rc = enqueue(hit->d_desc, true);
         hipError_t ce = hipStreamEndCapture(h->stream, &gr);
         if (rc) return rc;
         if (ce != hipSuccess) return hip_fail(h, ce, "hipStreamEndCapture");

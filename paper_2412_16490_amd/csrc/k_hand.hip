@@ -106,6 +106,7 @@ __global__ __launch_bounds__(kThreads) void hand_step_kernel(HandArgs a) {
     __shared__ float pose[kThreads][12];
     const Slot s = slot_of(a);
     const int tid = threadIdx.x;
+    if (a.clear && blockIdx.x == 0 && tid < 4) a.clear[tid] = 0;
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
     if (s.live) {
         const size_t idx = size_t(s.g) * a.M + s.i;
