@@ -16,7 +16,7 @@ namespace bodex {
 // group's scalars are in LDS: an early form with everything in registers (256,
 // and spills) took 1105 us at 5 contacts and 131,072 QPs, with these in LDS 862
 // (8 lanes per QP) and 734 (2 lanes).  At 629 us now (2 lanes), it and
-// newton_out_kernel (44 us) replace, for the pyramid, the one-lane and
+// newton_out_kernel (35 us) replace, for the pyramid, the one-lane and
 // contact-parallel active-set passes (1157 + 466 + 58 us).
 template <int MM, int GS, bool CONE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) newton_kernel(const KArgs a) {
@@ -117,9 +117,12 @@ __device__ inline NewtonRows newton_rows(int face, const NewtonFold& Y, double N
 // rounded state, without reading it back).  Streams the state out: 4 (6 m +
 // 18 m) B per QP at the pyramid's nine rows per contact.  QPs the Newton
 // method left are counted in KArgs::nfail and keep their ADMM point; their
-// outputs come from the finalize launch that follows.
+// outputs come from the finalize launch that follows.  Bound by HBM writes; at
+// three waves per SIMD (160 registers) nothing spills, at four 140 B a lane
+// did: 5 contacts, 131,072 QPs 43 -> 35 us, 951,279 QPs 417 -> 347, 8 contacts,
+// 8547 QPs 36 -> 22.
 template <int MM, bool CONE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) newton_out_kernel(const KArgs a) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) newton_out_kernel(const KArgs a) {
     constexpr int NV = 3 * MM, NG = 6 * NV, RW = CONE ? 3 : 9;
     extern __shared__ __align__(16) unsigned char smem[];
     FinPtrs<MM> P;
