@@ -100,18 +100,20 @@ struct KArgs {
     SpillPtrs spill;
     int* spill_count;
     int* spill_idx;
-    // dual Newton polish: per QP the dual solution u [6][W] and the result
-    // word (bodex_newton_kernels.h: bit 0 solved), and the number of QPs left;
-    // fin_mode 3: the finalize launch handles those alone
+    // dual Newton polish: per QP the dual solution u [6][W], or the forces
+    // [3 m][W] where u does not hold them, and the result word (newton_info),
+    // and the number of QPs left; fin_mode 3: the finalize launch handles
+    // those alone
     double* nu;
     int* ninfo;
     int* nfail;
 };
-// Word of ninfo: bit 0 solved, bit 1 not to be solved (non-finite input), 2-9
-// Newton steps, 10-17 evaluations, 18-31 line-search slopes.
-constexpr int kNewtonOk = 1, kNewtonSkip = 2;
+// Word of ninfo: bit 0 solved, bit 1 nu holds forces, 2-9 Newton steps, 10-17
+// evaluations, 18-31 line-search slopes; 0 = not to be solved (non-finite
+// input).
+constexpr int kNewtonOk = 1, kNewtonForces = 2;
 __device__ inline int newton_info(const NewtonOut& o) {
-    return int((o.ok ? 1u : 0u) | unsigned(min(o.steps, 255)) << 2 | unsigned(min(o.evals, 255)) << 10 |
+    return int((o.ok ? 1u : 0u) | (o.forces ? 2u : 0u) | unsigned(min(o.steps, 255)) << 2 | unsigned(min(o.evals, 255)) << 10 |
                unsigned(min(o.slopes, 16383)) << 18);
 }
 __device__ inline double newton_info_flops(int m, int info) {

@@ -24,6 +24,11 @@
 // 31), against 13 factorisations, 9 row steps and 6.5 row searches, each with
 // its own passes over the contacts, for the active-set polish.
 //
+// Rounding: y = G^T u / eps carries that of u, 1e-16 |beta t| / eps, which at
+// long torque arms or a large beta t exceeds what F has to fall below.  Such a
+// QP (newton_solve) is ended by newton_fine, which carries u and y in two
+// doubles each.
+//
 // Mapping: GS lanes per QP (1, 2, 4 or 8), lane `sub` owns the contacts sub,
 // sub + GS, ...; u, the 6 x 6 factor and the line search are replicated, the
 // sums over contacts are butterflies of DPP moves, whose pairwise additions
@@ -72,10 +77,10 @@ BODEX_FI void newton_contact(const double p[3], const double n[3], double kappa,
 // (12 doubles each, shared by the grasp's QPs), the proximal centre of its
 // contacts (entry e at centre[e * cs]), and the QP's beta t and schedule,
 // which the lanes of a group share (they write the same bits; entry e at
-// q[e * qs]).
+// q[e * qs]; in registers the two last cost another 1 % at 131,072 QPs).
 template <int NC>
 struct NewtonStore {
-    static constexpr int kGeo = 12, kCentre = 3 * NC, kQp = 16;
+    static constexpr int kGeo = 12, kCentre = 3 * NC, kQp = 18;
     const double* geo[NC];
     double* cp;
     int cs;
@@ -96,7 +101,37 @@ struct NewtonStore {
     BODEX_FI double& ratio() const { return q[8 * qs]; }  // of the proximal weight, and
     BODEX_FI double& last() const { return q[9 * qs]; }   // its last value before zero
     BODEX_FI double& ref(int r) const { return q[(10 + r) * qs]; }  // u some steps back
+    BODEX_FI double& end() const { return q[16 * qs]; }   // F's tolerance at the end,
+    BODEX_FI double& fine() const { return q[17 * qs]; }  // and whether newton_fine is the end
 };
+
+// A number as the sum of two doubles (hi the rounded value), by error-free
+// transformations: Knuth's sum, products with fma.  No contraction: the
+// compiler must not fuse one of their products into the sum that follows.
+struct NewtonTwo {
+    double hi, lo;
+};
+#if defined(__clang__)
+#define BODEX_NO_CONTRACT _Pragma("clang fp contract(off)")
+#else
+#define BODEX_NO_CONTRACT
+#endif
+BODEX_FI NewtonTwo two_sum(double a, double b) {
+    BODEX_NO_CONTRACT
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+BODEX_FI NewtonTwo two_add(NewtonTwo a, NewtonTwo b) {
+    BODEX_NO_CONTRACT
+    const NewtonTwo s = two_sum(a.hi, b.hi);
+    const double lo = s.lo + (a.lo + b.lo), hi = s.hi + lo;
+    return {hi, lo - (hi - s.hi)};
+}
+BODEX_FI NewtonTwo two_mul(double a, NewtonTwo b) {
+    BODEX_NO_CONTRACT
+    const double p = a * b.hi, lo = fma(a, b.hi, -p) + a * b.lo, hi = p + lo;
+    return {hi, lo - (hi - p)};
+}
 
 // R^T-rotated wrench: the contact's three rows of G^T w.
 BODEX_FI void newton_gt(const NewtonContact& C, const double* w, double* v) {
@@ -104,6 +139,21 @@ BODEX_FI void newton_gt(const NewtonContact& C, const double* w, double* v) {
                          w[2] + (w[3] * C.kp[1] - w[4] * C.kp[0])};
 #pragma unroll
     for (int t = 0; t < 3; ++t) v[t] = C.R[3 * t] * h[0] + C.R[3 * t + 1] * h[1] + C.R[3 * t + 2] * h[2];
+}
+
+// The same of w + dw.
+BODEX_FI void newton_gt_two(const NewtonContact& C, const double* w, const double* dw, NewtonTwo* v) {
+    NewtonTwo W[6], h[3];
+#pragma unroll
+    for (int r = 0; r < 6; ++r) W[r] = two_sum(w[r], dw[r]);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const int a = (t + 1) % 3, b = (t + 2) % 3;
+        h[t] = two_add(W[t], two_add(two_mul(C.kp[b], W[3 + a]), two_mul(-C.kp[a], W[3 + b])));
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+        v[t] = two_add(two_mul(C.R[3 * t], h[0]), two_add(two_mul(C.R[3 * t + 1], h[1]), two_mul(C.R[3 * t + 2], h[2])));
 }
 
 // The contact's vector v (normal, d, e) in the world frame.
@@ -167,6 +217,39 @@ BODEX_FI NewtonProj newton_project(const NewtonFold& y, const NewtonFriction& C,
     return P;
 }
 
+// Fold and projection of a point in two doubles: far from the cone f1 is what
+// is left of terms many times its size.
+template <bool CONE>
+BODEX_FI NewtonProj newton_project_two(const NewtonTwo (&y)[3], const NewtonFriction& C, double fmax, NewtonFold& Y) {
+    Y = newton_fold<CONE>(y[0].hi, y[1].hi, y[2].hi);
+    NewtonTwo p, q = {0.0, 0.0};
+    if constexpr (CONE) {  // the radius: a Newton step for the square root from its rounded value
+        const NewtonTwo sq = two_add(two_add(two_mul(y[1].hi, y[1]), two_mul(y[2].hi, y[2])),
+                                     {y[1].lo * y[1].hi + y[2].lo * y[2].hi, 0.0});
+        const double over = two_add(sq, two_mul(-Y.p, {Y.p, 0.0})).hi;
+        p = Y.p > 0.0 ? two_sum(Y.p, 0.5 * over / Y.p) : q;
+    } else {
+        p = two_add(two_mul(Y.a, y[1]), two_mul(Y.b, y[2]));
+        q = two_add(two_mul(Y.a, y[2]), two_mul(-Y.b, y[1]));
+        Y.q = q.hi;
+        if (q.hi < 0.0) q = {-q.hi, -q.lo};
+    }
+    Y.p = p.hi;
+    NewtonProj P;
+    const NewtonTwo t = two_add(y[0], two_mul(C.k, p));
+    P.ff = t.hi * C.i1;
+    P.m = __builtin_fmax(Y.y1, P.ff);
+    P.fe = 0.0;
+    if constexpr (!CONE) {
+        P.fe = two_add(t, two_mul(C.kt, q)).hi * C.i2;
+        P.m = __builtin_fmax(P.m, P.fe);
+    }
+    P.f1 = __builtin_fmin(__builtin_fmax(P.m, 0.0), fmax);
+    P.fp = __builtin_fmin(Y.p, C.k * P.f1);
+    P.fq = CONE ? 0.0 : copysign(__builtin_fmin(q.hi, C.kt * P.f1), Y.q);
+    return P;
+}
+
 // Its derivative w1 g g^T + w2 e_p e_p^T + w3 e_q e_q^T, g = (1, gp, gq).
 struct NewtonDeriv {
     double w1, gp, gq, w2, w3;
@@ -196,6 +279,61 @@ BODEX_FI int newton_face(const NewtonFold& y, const NewtonProj& P, const NewtonF
     const bool side = !(y.p < C.k * P.f1) && (P.m != y.y1 || P.m > fmax);
     const bool corner = !CONE && side && !(fabs(y.q) < C.kt * P.f1);
     return (P.m > fmax ? kNwCap : kNwFree) + (corner ? 2 : (side ? 1 : 0));
+}
+
+// Adds a contact's image G f to s[0..5] and its block G Pi G^T to s[6..26].
+BODEX_FI void newton_terms(const NewtonContact& C, const NewtonFold& Y, const NewtonProj& P, const NewtonDeriv& D,
+                           double* s) {
+    const double* kp = C.kp;
+    double w[3];
+    newton_world(C, P.f1, Y.a * P.fp - Y.b * P.fq, Y.b * P.fp + Y.a * P.fq, w);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) s[t] += w[t];
+    s[3] += kp[1] * w[2] - kp[2] * w[1];
+    s[4] += kp[2] * w[0] - kp[0] * w[2];
+    s[5] += kp[0] * w[1] - kp[1] * w[0];
+    // S = Pi in the world frame (3 x 3), then its force, torque-force
+    // and torque blocks with [kp]x
+    double ep[3], eq[3], g[3];
+    newton_world(C, 0.0, Y.a, Y.b, ep);
+    newton_world(C, 0.0, -Y.b, Y.a, eq);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) g[t] = C.R[t] + D.gp * ep[t] + D.gq * eq[t];
+    double S[3][3], w1g[3], w2p[3], w3q[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        w1g[t] = D.w1 * g[t];
+        w2p[t] = D.w2 * ep[t];
+        w3q[t] = D.w3 * eq[t];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            S[i][j] = w1g[i] * g[j] + w2p[i] * ep[j] + w3q[i] * eq[j];
+            S[j][i] = S[i][j];
+        }
+    double* M = s + 6;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) M[lo_idx(i, j)] += S[i][j];
+    double T[3][3];  // K S, K = [kp]x
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        T[0][j] = kp[1] * S[2][j] - kp[2] * S[1][j];
+        T[1][j] = kp[2] * S[0][j] - kp[0] * S[2][j];
+        T[2][j] = kp[0] * S[1][j] - kp[1] * S[0][j];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) M[lo_idx(3 + i, j)] += T[i][j];
+        // (K S) K^T, lower triangle: row i of T crossed with kp
+        M[lo_idx(3 + i, 3)] += T[i][2] * kp[1] - T[i][1] * kp[2];
+        if (i >= 1) M[lo_idx(3 + i, 4)] += T[i][0] * kp[2] - T[i][2] * kp[0];
+        if (i >= 2) M[lo_idx(3 + i, 5)] += T[i][1] * kp[0] - T[i][0] * kp[1];
+    }
 }
 
 // Reciprocal to the last bits (pivots of the factorisation, positive).
@@ -300,8 +438,22 @@ constexpr double kNewtonTol = 2e-9;  // |F|_inf relative to |beta t|
 
 constexpr int kNewtonSteps = 200;      // cap on the Newton steps of a QP
 
+// The last proximal weight is at most this many eps.  Beyond a mean squared
+// length of 20 (the workloads' contacts reach 8) the schedules above would
+// leave a wider and wider gap down to eps, which the line search at weight
+// zero has to bridge: torque_scale 400 / 1000 / 4000, slopes per QP 160 / 219 /
+// 279 without the limit, 85 / 97 / 111 with it.
+constexpr double kProxLast = 4000.0;
+
+// A QP is ended by newton_fine when the rounding of y exceeds kFineForce (the
+// forces' own error against it: 1e-10 up to there), or that of F its
+// tolerance; F's tolerance until then: kFineTol times its rounding.
+constexpr double kFineForce = 1e-9, kFineTol = 4.0;
+constexpr int kFineSteps = 6;
+
 struct NewtonOut {
     int ok, steps, evals, slopes;
+    int forces;  // the forces are in the store's centre (newton_fine)
 };
 
 // Algorithmic FP64 flops of one solve (FMA = 2, add/mul/div = 1, selects and
@@ -313,13 +465,79 @@ BODEX_FI double newton_flops(int m, int steps, int evals, int slopes) {
     return 254.0 * m + evals * (236.0 * m) + steps * (30.0 * m + 235.0) + slopes * (51.0 * m + 9.0);
 }
 
-// Solve one QP: u <- the dual solution.  st holds the lane's contacts, beta t
+// Puts a contact's projection into the store's centre.
+template <int NC>
+BODEX_FI void newton_keep(const NewtonStore<NC>& st, int c, const NewtonFold& Y, const NewtonProj& P) {
+    st.centre(c, 0) = P.f1;
+    st.centre(c, 1) = Y.a * P.fp - Y.b * P.fq;
+    st.centre(c, 2) = Y.b * P.fp + Y.a * P.fq;
+}
+
+// Newton steps at weight zero on u + lo, with y and its projection in two
+// doubles: F then falls to the rounding of its own sum, whatever |u| / eps.  The
+// forces, which u alone does not hold, are left in the store's centre.  Largest
+// force error of 4800 QPs (5 contacts, cold starts) without / with it: beta 100
+// 2e-8 / 7e-15, beta 1000 1e-7 / 5e-14; torque arms of 50: 123 QPs above the
+// tolerance after 128 steps / none, of 200: 829 / none.  Whole solve on the GPU,
+// 131,072 QPs, torque_scale 400 / 1000 / 4000: 10.6 / 16.9 / 20.4 ms without, 1.05
+// / 1.16 / 1.41 with; at beta 100, where it adds an iteration, 0.60 / 0.63.
+template <int GS, int NC, bool CONE>
+BODEX_FI bool newton_fine(const NewtonStore<NC>& st, const NewtonFriction (&Fr)[NC], double fm, double eps,
+                          const double (&u)[6], NewtonOut& out) {
+    const double ie = 1.0 / eps;
+    double lo[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+        BODEX_SPLIT();
+        ++out.evals;
+        double s[27];
+#pragma unroll
+        for (int j = 0; j < 27; ++j) s[j] = 0.0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const NewtonContact C = st.contact(c);
+            NewtonTwo y[3];
+            newton_gt_two(C, u, lo, y);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) y[t] = two_mul(ie, y[t]);
+            NewtonFold Y;
+            const NewtonProj P = newton_project_two<CONE>(y, Fr[c], fm, Y);
+            newton_terms(C, Y, P, newton_deriv<CONE>(Y, P, Fr[c], fm), s);
+            newton_keep(st, c, Y, P);
+            BODEX_SPLIT();
+        }
+        group_sum<GS>(s);
+        double res = 0.0, all = 0.0, d[6];
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            d[r] = s[r] + ((u[r] - st.bt(r)) + lo[r]);
+            res = __builtin_fmax(res, fabs(d[r]));
+            all += fabs(d[r]);
+        }
+        if (!(all < INFINITY)) return false;
+        if ((k > 0 && res <= 1e-3 * st.end()) || k == kFineSteps) return res <= st.end();
+        double* M = s + 6;
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            d[r] *= -eps;
+            M[lo_idx(r, r)] += eps;
+        }
+        if (!ldl6(M)) return false;
+        ldl6_solve(M, d);
+#pragma unroll
+        for (int r = 0; r < 6; ++r) lo[r] += d[r];
+        ++out.steps;
+    }
+}
+
+// Solve one QP: u <- the dual solution (NewtonOut::forces: the forces are in the
+// centre, and of u only its rounding).  st holds the lane's contacts, beta t
 // and the starting forces (the proximal centre, overwritten), Fr the contacts'
 // friction terms, m the contacts of the grasp.  Every lane of the group calls it.
 template <int GS, int NC, bool CONE>
 BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction (&Fr)[NC], int m, double fm, double eps,
                                 int max_steps, double (&u)[6]) {
-    NewtonOut out = {0, 0, 0, 0};
+    NewtonOut out = {0, 0, 0, 0, 0};
     // u = beta t - G f
     double len[1] = {0.0};
     {
@@ -346,12 +564,19 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
     double t2 = 0.0;
 #pragma unroll
     for (int r = 0; r < 6; ++r) t2 += st.bt(r) * st.bt(r);
-    st.tol() = kNewtonTol * sqrt(t2) + 1e-12 * fm;
+    st.end() = kNewtonTol * sqrt(t2) + 1e-12 * fm;
     group_sum<GS>(len);
     st.scale() = len[0] / m;
+    // the rounding of u / eps; times a row of G that of y, times its square that of F
+    {
+        const double noise = 0x1p-53 * sqrt(t2) / eps;
+        const bool fine = noise * sqrt(st.scale()) > kFineForce || noise * st.scale() > kNewtonTol * sqrt(t2);
+        st.fine() = fine ? 1.0 : 0.0;
+        st.tol() = fine ? fmax(st.end(), kFineTol * noise * st.scale()) : st.end();
+    }
     const ProxSchedule first = CONE ? kProxCone : kProxPyramid;
     st.ratio() = first.ratio;
-    st.last() = fmax(first.last * st.scale(), 10.0 * eps);
+    st.last() = fmax(fmin(first.last * st.scale(), kProxLast * eps), 10.0 * eps);
     double prox = first.first * st.scale();
     if (prox < 10.0 * eps) prox = 0.0;
     int at_zero = 0, rounds = 0;
@@ -374,56 +599,7 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
             const NewtonFold Y = newton_fold<CONE>(y[c][0], y[c][1], y[c][2]);
             const NewtonProj P = newton_project<CONE>(Y, Fr[c], fm);
             const NewtonDeriv D = newton_deriv<CONE>(Y, P, Fr[c], fm);
-            const double* kp = C.kp;
-            double w[3];
-            newton_world(C, P.f1, Y.a * P.fp - Y.b * P.fq, Y.b * P.fp + Y.a * P.fq, w);
-#pragma unroll
-            for (int t = 0; t < 3; ++t) s[t] += w[t];
-            s[3] += kp[1] * w[2] - kp[2] * w[1];
-            s[4] += kp[2] * w[0] - kp[0] * w[2];
-            s[5] += kp[0] * w[1] - kp[1] * w[0];
-            // S = Pi in the world frame (3 x 3), then its force, torque-force
-            // and torque blocks with [kp]x
-            double ep[3], eq[3], g[3];
-            newton_world(C, 0.0, Y.a, Y.b, ep);
-            newton_world(C, 0.0, -Y.b, Y.a, eq);
-#pragma unroll
-            for (int t = 0; t < 3; ++t) g[t] = C.R[t] + D.gp * ep[t] + D.gq * eq[t];
-            double S[3][3], w1g[3], w2p[3], w3q[3];
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                w1g[t] = D.w1 * g[t];
-                w2p[t] = D.w2 * ep[t];
-                w3q[t] = D.w3 * eq[t];
-            }
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j <= i; ++j) {
-                    S[i][j] = w1g[i] * g[j] + w2p[i] * ep[j] + w3q[i] * eq[j];
-                    S[j][i] = S[i][j];
-                }
-            double* M = s + 6;
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j <= i; ++j) M[lo_idx(i, j)] += S[i][j];
-            double T[3][3];  // K S, K = [kp]x
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                T[0][j] = kp[1] * S[2][j] - kp[2] * S[1][j];
-                T[1][j] = kp[2] * S[0][j] - kp[0] * S[2][j];
-                T[2][j] = kp[0] * S[1][j] - kp[1] * S[0][j];
-            }
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-#pragma unroll
-                for (int j = 0; j < 3; ++j) M[lo_idx(3 + i, j)] += T[i][j];
-                // (K S) K^T, lower triangle: row i of T crossed with kp
-                M[lo_idx(3 + i, 3)] += T[i][2] * kp[1] - T[i][1] * kp[2];
-                if (i >= 1) M[lo_idx(3 + i, 4)] += T[i][0] * kp[2] - T[i][2] * kp[0];
-                if (i >= 2) M[lo_idx(3 + i, 5)] += T[i][1] * kp[0] - T[i][0] * kp[1];
-            }
+            newton_terms(C, Y, P, D, s);
         }
         group_sum<GS>(s);
         double res = 0.0, all = 0.0, d[6];
@@ -540,7 +716,7 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
             recentre = true;
             prox = kProxRestart.first / kProxRestart.ratio * st.scale();
             st.ratio() = kProxRestart.ratio;
-            st.last() = fmax(kProxRestart.last * st.scale(), 10.0 * eps);
+            st.last() = fmax(fmin(kProxRestart.last * st.scale(), kProxLast * eps), 10.0 * eps);
         }
         if (recentre) {
 #pragma unroll
@@ -549,15 +725,13 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
 #pragma unroll
                 for (int t = 0; t < 3; ++t) v[t] = al == 0.0 ? y[c][t] : y[c][t] + al * dy[c][t];
                 const NewtonFold Y = newton_fold<CONE>(v[0], v[1], v[2]);
-                const NewtonProj P = newton_project<CONE>(Y, Fr[c], fm);
-                st.centre(c, 0) = P.f1;
-                st.centre(c, 1) = Y.a * P.fp - Y.b * P.fq;
-                st.centre(c, 2) = Y.b * P.fp + Y.a * P.fq;
+                newton_keep(st, c, Y, newton_project<CONE>(Y, Fr[c], fm));
             }
             prox *= st.ratio();
             if (prox < st.last()) prox = 0.0;
         }
     }
+    if (out.ok && st.fine() != 0.0) out.ok = out.forces = newton_fine<GS, NC, CONE>(st, Fr, fm, eps, u, out) ? 1 : 0;
     return out;
 }
 

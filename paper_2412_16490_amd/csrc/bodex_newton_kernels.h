@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ne
     const SlotInfo si = sInfo[slot];
     const int w = si.w0 + j;
     if (a.status[w] & kStNonfinite) {
-        if (sub == 0) a.ninfo[w] = kNewtonSkip;
+        if (sub == 0) a.ninfo[w] = 0;
         return;
     }
     const size_t sw = state_col(a, si, j);
@@ -74,11 +74,19 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ne
     for (int r = 0; r < 6; ++r) store.bt(r) = double(a.beta) * double(a.wrench[size_t(w) * 6 + r]);
     const NewtonOut o = newton_solve<GS, NC, CONE>(store, Fr, si.m, double(a.fmax), double(a.eps),
                                                    min(a.polish_steps, kNewtonSteps), u);
-    if (sub == 0) {
+    if (o.forces) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int i = sub + GS * c;
+            if (i < si.m)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a.nu[size_t(3 * i + q) * a.W + w] = store.centre(c, q);
+        }
+    } else if (sub == 0) {
 #pragma unroll
         for (int r = 0; r < 6; ++r) a.nu[size_t(r) * a.W + w] = u[r];
-        a.ninfo[w] = newton_info(o);
     }
+    if (sub == 0) a.ninfo[w] = newton_info(o);
 }
 
 // Multipliers of a pyramid contact's nine rows from its normal-cone vector
@@ -155,7 +163,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
         for (int r = 0; r < 6; ++r) bt[r] = double(a.beta) * double(a.wrench[size_t(w) * 6 + r]);
         if (finite_in && (info & kNewtonOk)) {
             const double eps = double(a.eps), ie = 1.0 / eps, fm = double(a.fmax);
-            double u[6];
+            const bool forces = info & kNewtonForces;
+            double u[6];  // (of a QP whose forces are stored: below)
 #pragma unroll
             for (int r = 0; r < 6; ++r) u[r] = a.nu[size_t(r) * a.W + w];
             NewtonFriction Fr;  // of contact i
@@ -172,6 +181,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
                 Y = newton_fold<CONE>(gu[0] * ie, gu[1] * ie, gu[2] * ie);
                 return newton_project<CONE>(Y, Fr, fm);
             };
+            // its forces: as stored, or that projection's
+            auto force = [&](int i, const NewtonFold& Y, const NewtonProj& p, double* f) {
+                f[0] = p.f1;
+                f[1] = Y.a * p.fp - Y.b * p.fq;
+                f[2] = Y.b * p.fp + Y.a * p.fq;
+                if (forces) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) f[t] = a.nu[size_t(3 * i + t) * a.W + w];
+                }
+            };
             double r6[6], gx[6], ff = 0.0, s1 = 0.0;
 #pragma unroll
             for (int r = 0; r < 6; ++r) {
@@ -185,9 +204,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
                     double gu[3];
                     NewtonFold Y;
                     const NewtonProj p = contact(i, gu, Y);
-                    f[0] = p.f1;
-                    f[1] = Y.a * p.fp - Y.b * p.fq;
-                    f[2] = Y.b * p.fp + Y.a * p.fq;
+                    force(i, Y, p, f);
 #pragma unroll
                     for (int t = 0; t < 3; ++t)
 #pragma unroll
@@ -205,6 +222,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
                     a.forces[size_t(w) * 3 * a.ms + 3 * i + t] = float(f[t]);
                 }
             }
+            if (forces) {
+#pragma unroll
+                for (int r = 0; r < 6; ++r) u[r] = -r6[r];
+            }
             // z, y and the residual of the rounded state
             double rp = 0, nAx = 0, nz = 0, rd = 0, nPx = 0, nAty = 0, nq = 0, t1 = 0.0;
 #pragma unroll 1
@@ -218,8 +239,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
                     const NewtonProj p = contact(i, gu, Y);
                     const double k = muc[i];
                     const int face = newton_face<CONE>(Y, p, Fr, fm);
-                    const double f[3] = {p.f1, Y.a * p.fp - Y.b * p.fq, Y.b * p.fp + Y.a * p.fq};
-                    double N[3], x[3], aty[3] = {0.0, 0.0, 0.0};
+                    double f[3], N[3], x[3], aty[3] = {0.0, 0.0, 0.0};
+                    force(i, Y, p, f);
 #pragma unroll
                     for (int t = 0; t < 3; ++t) {
                         N[t] = 2.0 * (gu[t] - eps * f[t]);

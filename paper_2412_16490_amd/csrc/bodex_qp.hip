@@ -450,8 +450,8 @@ int newton_group(int mm, bool cone, int n_qps) {
 // QP of the batch, so none is ever finished in the first pass for want of
 // room) in a; chunked is false where the chunked polish does not apply (no
 // polish, the circular cone, gamma > 0, chunk 0: effective()).
-// The dual Newton polish takes u and a result word per QP from the same
-// workspace (less than the records need); for the cone, which needs none
+// The dual Newton polish takes u or the forces and a result word per QP from the
+// same workspace (less than the records need); for the cone, which needs none
 // otherwise, only where the budget has room beside `reserve`, the bytes the
 // call allocates after this, and the one-lane barrier polish runs where not.
 int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, size_t reserve, bool& chunked, int& grid_g) {
@@ -462,13 +462,13 @@ int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, size_t reserve, bool& chun
     if (!chunked && !newton) return 0;
     const size_t K = size_t(W);
     const size_t nd = size_t(3 * mm + 3) * K, ni = size_t(bodex::kSpInts) * K + size_t(W);
-    const size_t need = chunked ? nd * sizeof(double) + ni * sizeof(int) : K * (6 * sizeof(double) + sizeof(int));
+    const size_t need = chunked ? nd * sizeof(double) + ni * sizeof(int) : K * (3 * mm * sizeof(double) + sizeof(int));
     if (!chunked && h->owned_bytes - h->d_spill_cap + std::max(need, h->d_spill_cap) + reserve > h->budget) return 0;
     const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, need);
     if (rc) return rc;
     if (newton) {
         a.nu = static_cast<double*>(h->d_spill);
-        a.ninfo = reinterpret_cast<int*>(a.nu + 6 * K);
+        a.ninfo = reinterpret_cast<int*>(a.nu + 3 * mm * K);
         chunked = false;
         return 0;
     }
