@@ -100,10 +100,12 @@ struct KArgs {
     SpillPtrs spill;
     int* spill_count;
     int* spill_idx;
-    // dual Newton polish: per QP the dual solution u [6][W], or the forces
-    // [3 m][W] where u does not hold them, and the result word (newton_info),
-    // and the number of QPs left; fin_mode 3: the finalize launch handles
-    // those alone
+    // dual Newton polish (newton): of the pyramid per QP the dual solution u
+    // [6][W], or the forces [3 m][W] where u does not hold them, and the result
+    // word (newton_info); the cone keeps the forces in the rows of z and y that
+    // its outputs overwrite, and the word in qobj; the number of QPs left.
+    // fin_mode 3: the finalize launch handles those alone
+    int newton;
     double* nu;
     int* ninfo;
     int* nfail;
@@ -116,6 +118,13 @@ __device__ inline int newton_info(const NewtonOut& o) {
     return int((o.ok ? 1u : 0u) | (o.forces ? 2u : 0u) | unsigned(min(o.steps, 255)) << 2 | unsigned(min(o.evals, 255)) << 10 |
                unsigned(min(o.slopes, 16383)) << 18);
 }
+// The word of QP w (of the cone: until its objective is written).
+__device__ __forceinline__ int newton_word(const KArgs& a, int w) {
+    return a.ninfo ? a.ninfo[w] : __float_as_int(a.qobj[w]);
+}
+// Whether the outputs of QP w are still to come from the finalize launch: only
+// they set the bit, ADMM's status never holds it.
+__device__ __forceinline__ bool newton_left(const KArgs& a, int w) { return !(a.status[w] & kStPolished); }
 __device__ inline double newton_info_flops(int m, int info) {
     const unsigned v = unsigned(info);
     return (v >> 10) & 255 ? newton_flops(m, (v >> 2) & 255, (v >> 10) & 255, v >> 18) : 0.0;
@@ -894,7 +903,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
         SlotInfo si = {0, 0, 1, 0};
         if (act) si = P.info[slot];
         const int w = si.w0 + j;
-        const bool left = rest && act && !(a.ninfo[w] & kNewtonOk);
+        const bool left = rest && act && newton_left(a, w);
         if (rest && !__syncthreads_or(left)) continue;
         // this lane's spill record (-1: none)
         int kspill = (act && mode == 2) ? a.spill_idx[w] : -1;
@@ -987,7 +996,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
             if (!skip) {
                 if (ran) {
                     if (a.pflops)
-                        a.pflops[w] = float(polish_flops(si.m, po) + (rest ? newton_info_flops(si.m, a.ninfo[w]) : 0.0));
+                        a.pflops[w] = float(polish_flops(si.m, po) + (rest ? newton_info_flops(si.m, newton_word(a, w)) : 0.0));
                     if (po.status == 0) {
                         polished = true;
                         st |= kStPolished;
@@ -1240,7 +1249,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
         SlotInfo si = {0, 0, 1, 0};
         if (act) si = P.info[slot];
         const int w = si.w0 + j;
-        const bool left = rest && act && !(a.ninfo[w] & kNewtonOk);
+        const bool left = rest && act && newton_left(a, w);
         if (rest && !__syncthreads_or(left)) continue;
         const bool good = fin_setup<MM>(a, P, nsl, slot, j, si, true);
         double Q = 0.0;
@@ -1283,7 +1292,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
                 }
                 if (a.pflops)
                     a.pflops[w] = float(cone_polish_flops(si.m, po) +
-                                        (rest ? newton_info_flops(si.m, a.ninfo[w]) : 0.0));
+                                        (rest ? newton_info_flops(si.m, newton_word(a, w)) : 0.0));
                 if (po.status == 0) {
                     polished = true;
                     st |= kStPolished;

@@ -453,7 +453,7 @@ constexpr int kFineSteps = 6;
 
 struct NewtonOut {
     int ok, steps, evals, slopes;
-    int forces;  // the forces are in the store's centre (newton_fine)
+    int forces;  // the forces are in the store's centre (newton_fine; always of the cone)
 };
 
 // Algorithmic FP64 flops of one solve (FMA = 2, add/mul/div = 1, selects and
@@ -613,6 +613,14 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
         const bool small = res <= (prox > 0.0 ? 1e3 * st.tol() : st.tol());
         if (small && prox == 0.0) {
             out.ok = 1;
+            if constexpr (CONE) {
+                out.forces = 1;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const NewtonFold Y = newton_fold<CONE>(y[c][0], y[c][1], y[c][2]);
+                    newton_keep(st, c, Y, newton_project<CONE>(Y, Fr[c], fm));
+                }
+            }
             break;
         }
         if (out.steps >= max_steps) break;

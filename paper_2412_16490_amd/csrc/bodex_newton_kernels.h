@@ -8,6 +8,26 @@
 
 namespace bodex {
 
+// The cone's force c of a QP between the two kernels: its words in row c of z
+// and of y at state column sw.
+__device__ __forceinline__ void cone_keep(const KArgs& a, int c, size_t sw, double f) {
+    const long long b = __double_as_longlong(f);
+    a.z[size_t(c) * a.sW + sw] = __int_as_float(int(b));
+    a.y[size_t(c) * a.sW + sw] = __int_as_float(int(b >> 32));
+}
+template <bool CONE>
+__device__ __forceinline__ void newton_keep_word(const KArgs& a, int w, int word) {
+    if constexpr (CONE)
+        a.qobj[w] = __int_as_float(word);
+    else
+        a.ninfo[w] = word;
+}
+__device__ __forceinline__ double cone_kept(const KArgs& a, int c, size_t sw) {
+    const unsigned lo = unsigned(__float_as_int(a.z[size_t(c) * a.sW + sw]));
+    const unsigned hi = unsigned(__float_as_int(a.y[size_t(c) * a.sW + sw]));
+    return __longlong_as_double((static_cast<long long>(hi) << 32) | lo);
+}
+
 // Solve: GS lanes per QP, 64 / GS QPs per one-wave workgroup; the GS parts of
 // a tile are separate workgroups, so a hard QP holds up no more than the
 // other groups of its wave.  Bound by FP64 issue and the dependent chain of
@@ -49,7 +69,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ne
     const SlotInfo si = sInfo[slot];
     const int w = si.w0 + j;
     if (a.status[w] & kStNonfinite) {
-        if (sub == 0) a.ninfo[w] = 0;
+        if (sub == 0) newton_keep_word<CONE>(a, w, 0);
         return;
     }
     const size_t sw = state_col(a, si, j);
@@ -74,19 +94,24 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ne
     for (int r = 0; r < 6; ++r) store.bt(r) = double(a.beta) * double(a.wrench[size_t(w) * 6 + r]);
     const NewtonOut o = newton_solve<GS, NC, CONE>(store, Fr, si.m, double(a.fmax), double(a.eps),
                                                    min(a.polish_steps, kNewtonSteps), u);
-    if (o.forces) {
+    if (o.ok && o.forces) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const int i = sub + GS * c;
             if (i < si.m)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) a.nu[size_t(3 * i + q) * a.W + w] = store.centre(c, q);
+                for (int q = 0; q < 3; ++q) {
+                    if constexpr (CONE)
+                        cone_keep(a, 3 * i + q, sw, store.centre(c, q));
+                    else
+                        a.nu[size_t(3 * i + q) * a.W + w] = store.centre(c, q);
+                }
         }
-    } else if (sub == 0) {
+    } else if (!CONE && sub == 0) {
 #pragma unroll
         for (int r = 0; r < 6; ++r) a.nu[size_t(r) * a.W + w] = u[r];
     }
-    if (sub == 0) a.ninfo[w] = newton_info(o);
+    if (sub == 0) newton_keep_word<CONE>(a, w, newton_info(o));
 }
 
 // Multipliers of a pyramid contact's nine rows from its normal-cone vector
@@ -156,17 +181,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
         const int w = si.w0 + j;
         const size_t W_ = size_t(a.sW), sw = state_col(a, si, j);
         unsigned char st = a.status[w];
-        const int info = a.ninfo[w];
+        const int info = newton_word(a, w);
         const bool finite_in = good && !(st & kStNonfinite);
         double bt[6];
 #pragma unroll
         for (int r = 0; r < 6; ++r) bt[r] = double(a.beta) * double(a.wrench[size_t(w) * 6 + r]);
         if (finite_in && (info & kNewtonOk)) {
             const double eps = double(a.eps), ie = 1.0 / eps, fm = double(a.fmax);
-            const bool forces = info & kNewtonForces;
+            const bool forces = CONE || (info & kNewtonForces);
             double u[6];  // (of a QP whose forces are stored: below)
 #pragma unroll
-            for (int r = 0; r < 6; ++r) u[r] = a.nu[size_t(r) * a.W + w];
+            for (int r = 0; r < 6; ++r) u[r] = CONE ? 0.0 : a.nu[size_t(r) * a.W + w];
             NewtonFriction Fr;  // of contact i
             // contact i's G^T u, folded point and projection
             auto contact = [&](int i, double* gu, NewtonFold& Y) -> NewtonProj {
@@ -188,7 +213,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
                 f[2] = Y.b * p.fp + Y.a * p.fq;
                 if (forces) {
 #pragma unroll
-                    for (int t = 0; t < 3; ++t) f[t] = a.nu[size_t(3 * i + t) * a.W + w];
+                    for (int t = 0; t < 3; ++t)
+                        f[t] = CONE ? cone_kept(a, 3 * i + t, sw) : a.nu[size_t(3 * i + t) * a.W + w];
                 }
             };
             double r6[6], gx[6], ff = 0.0, s1 = 0.0;

@@ -280,16 +280,6 @@ int ensure_device(bodex_qp* h, void** ptr, size_t* cap, size_t need) {
         drop_graphs(h);
     }
     size_t extra = need - *cap;
-    // the cone's polish workspace makes room (it is set up after every other
-    // allocation of a call, and only where it fits)
-    if (h->owned_bytes + extra > h->budget && h->d_spill && ptr != &h->d_spill &&
-        h->prm.friction_cone == BODEX_CONE_CIRCULAR) {
-        HIP_TRY(h, hipStreamSynchronize(h->stream));
-        HIP_TRY(h, hipFree(h->d_spill));
-        h->owned_bytes -= h->d_spill_cap;
-        h->d_spill = nullptr;
-        h->d_spill_cap = 0;
-    }
     if (h->owned_bytes + extra > h->budget)
         return fail(h, BODEX_EBUDGET, "workspace of %zu bytes exceeds the budget of %zu bytes",
                     h->owned_bytes + extra, h->budget);
@@ -451,22 +441,19 @@ int newton_group(int mm, bool cone, int n_qps) {
 // room) in a; chunked is false where the chunked polish does not apply (no
 // polish, the circular cone, gamma > 0, chunk 0: effective()).
 // The dual Newton polish takes u or the forces and a result word per QP from the
-// same workspace (less than the records need); for the cone, which needs none
-// otherwise, only where the budget has room beside `reserve`, the bytes the
-// call allocates after this, and the one-lane barrier polish runs where not.
-int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, size_t reserve, bool& chunked, int& grid_g) {
+// same workspace (less than the records need); the cone's keeps them in the
+// state and needs none, so that its results do not hang on the budget.
+int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, bool& chunked, int& grid_g) {
     const int chunk = effective(h->prm, W).polish_chunk;
-    const bool newton = newton_applies(h->prm, W);
+    a.newton = newton_applies(h->prm, W) ? 1 : 0;
     chunked = chunk > 0;
     grid_g = 0;
-    if (!chunked && !newton) return 0;
+    if (!chunked) return 0;
     const size_t K = size_t(W);
     const size_t nd = size_t(3 * mm + 3) * K, ni = size_t(bodex::kSpInts) * K + size_t(W);
-    const size_t need = chunked ? nd * sizeof(double) + ni * sizeof(int) : K * (3 * mm * sizeof(double) + sizeof(int));
-    if (!chunked && h->owned_bytes - h->d_spill_cap + std::max(need, h->d_spill_cap) + reserve > h->budget) return 0;
-    const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, need);
+    const int rc = ensure_device(h, &h->d_spill, &h->d_spill_cap, nd * sizeof(double) + ni * sizeof(int));
     if (rc) return rc;
-    if (newton) {
+    if (a.newton) {
         a.nu = static_cast<double*>(h->d_spill);
         a.ninfo = reinterpret_cast<int*>(a.nu + 3 * mm * K);
         chunked = false;
@@ -489,7 +476,7 @@ int chunk_setup(bodex_qp* h, KArgs& a, int W, int mm, size_t reserve, bool& chun
 int enqueue_finalize(bodex_qp* h, KArgs f, int mm, bool chunked, int* d_queue, int grid_f, int grid_g,
                      size_t lds_f) {
     f.queue = nullptr;
-    if (f.nu) {
+    if (f.newton) {
         f.nfail = d_queue + 2;
         const int gs = newton_group(mm, f.cone != 0, f.W);
         HIP_TRY(h, f.cone ? bodex::launch_newton_cone(mm, gs, f, h->stream) : bodex::launch_newton(mm, gs, f, h->stream));
@@ -852,7 +839,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
     bool chunked = false;
     int grid_g = 0;
     const size_t n_ints = desc_ints(G, S, lay);
-    rc = chunk_setup(h, a, W, mm, n_ints * sizeof(int), chunked, grid_g);
+    rc = chunk_setup(h, a, W, mm, chunked, grid_g);
     if (rc) return rc;
 
     const bool timing = (h->prm.flags & BODEX_F_TIMING) != 0;
@@ -898,7 +885,7 @@ int bodex_qp_solve(bodex_qp_t* h, const bodex_batch* in, bodex_result* out) {
         if (rc) return rc;
         rc = enqueue(h->d_desc, timing, false);
         if (rc) return rc;
-        h->last_launches = (a.nu || chunked) ? 4 : 2;
+        h->last_launches = (a.newton || chunked) ? 4 : 2;
         h->t_admm = h->t_fin = timing;
         return 0;
     }
@@ -1294,7 +1281,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
     const int grid_a = batched ? occupancy_grid(h, per_cu, S.n_tiles) : S.n_tiles;
     bool chunked = false;
     int grid_g = 0;
-    rc = chunk_setup(h, a, W, mm, n_ints * sizeof(int), chunked, grid_g);
+    rc = chunk_setup(h, a, W, mm, chunked, grid_g);
     if (rc) return rc;
 
     // The whole descent for the descriptors at `desc`: loss weights, the
@@ -1357,7 +1344,7 @@ int bodex_qp_descend(bodex_qp_t* h, const bodex_hand* hand, const bodex_batch* q
         if (rc) return rc;
         rc = enqueue(h->d_desc, false);
         if (rc) return rc;
-        h->last_launches = 2 + ((a.nu || chunked) ? 6 : 4) * d->iters;
+        h->last_launches = 2 + ((a.newton || chunked) ? 6 : 4) * d->iters;
         return 0;
     }
     // Graph path: the descent's launches captured once per shape, pointers
