@@ -118,15 +118,15 @@ typedef struct {
     int polish_steps;     /* cap on the steps of the polish (Newton steps;    */
                           /* active-set corrections)                          */
     int polish_chunk;     /* 0 = the one-lane active-set polish; otherwise    */
-                          /* the pyramid with gamma = 0 and eps_reg >= 5e-7   */
-                          /* takes the dual Newton polish.  Where that does   */
-                          /* not apply: factorisations a QP takes in the      */
-                          /* one-lane FP64 polish before it is handed to the  */
-                          /* contact-parallel polish (a group of lanes, one   */
-                          /* per contact); -1 = chosen by the number of QPs   */
-                          /* (1 up to 40,960, else 16).  A QP is also handed  */
-                          /* on at its next factorisation once at most 8      */
-                          /* lanes of its wavefront still polish.             */
+                          /* the pyramid with gamma = 0, eps_reg >= 5e-7 and  */
+                          /* polish_steps >= 32 takes the dual Newton polish. */
+                          /* Where that does not apply: factorisations a QP   */
+                          /* takes in the one-lane FP64 polish before it is   */
+                          /* handed to the contact-parallel polish (a group   */
+                          /* of lanes, one per contact); -1 = chosen by the   */
+                          /* number of QPs (1 up to 40,960, else 16).  A QP   */
+                          /* is also handed on at its next factorisation once */
+                          /* at most 8 lanes of its wavefront still polish.   */
                           /* Used with BODEX_F_POLISH, the pyramid and        */
                           /* gamma = 0.                                       */
     unsigned flags;       /* BODEX_F_*                                        */

@@ -413,9 +413,16 @@ hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStrea
 // sees a difference beyond the force tolerance's scale in one of 60 cases at
 // most, and large batches keep the forces they had.
 constexpr int kConeNewtonQps = 8192;
+// Under a smaller step cap the pyramid's Newton solves leave QPs in every tile to
+// the one-lane polish, and both cost more than the chunked polish alone does.
+// Measured, us, chunked / Newton, 16 wrenches, cap 16, 24, 32: 5 contacts, 64
+// grasps 685 / 1395, 667 / 499, 706 / 219, 8192 grasps 2164 / 4803, 2246 / 1848,
+// 2210 / 1212; 8 contacts x 11, 1024 grasps 1220 / 3168, 1436 / 1850, 1543 / 381.
+constexpr int kNewtonMinSteps = 32;
 bool newton_applies(const bodex_qp_params& p, int n_qps) {
-    return (p.flags & BODEX_F_POLISH) && p.gamma == 0.f && p.polish_chunk != 0 && p.polish_steps > 0 &&
-           p.eps_reg >= 5e-7f && (p.friction_cone == BODEX_CONE_PYRAMID8 || n_qps <= kConeNewtonQps);
+    const bool pyramid = p.friction_cone == BODEX_CONE_PYRAMID8;
+    return (p.flags & BODEX_F_POLISH) && p.gamma == 0.f && p.polish_chunk != 0 && p.eps_reg >= 5e-7f &&
+           (pyramid ? p.polish_steps >= kNewtonMinSteps : p.polish_steps > 0 && n_qps <= kConeNewtonQps);
 }
 
 // Lanes per QP.  More lanes shorten the chain of a QP's steps, fewer waste
