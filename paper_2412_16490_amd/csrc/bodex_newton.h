@@ -564,7 +564,9 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
     double t2 = 0.0;
 #pragma unroll
     for (int r = 0; r < 6; ++r) t2 += st.bt(r) * st.bt(r);
-    st.end() = kNewtonTol * sqrt(t2) + 1e-12 * fm;
+    // the second term grows neither with an fmax that no force reaches nor against
+    // a small beta t; the third ends a solve of beta t = 0 from other forces
+    st.end() = kNewtonTol * sqrt(t2) + 1e-12 * fmin(fm, 1.0) * fmin(1e3 * sqrt(t2), 1.0) + 1e-24;
     group_sum<GS>(len);
     st.scale() = len[0] / m;
     // the rounding of u / eps; times a row of G that of y, times its square that of F

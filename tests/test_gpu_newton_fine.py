@@ -75,3 +75,17 @@ def test_cone(m, kw):
     ref = oc.solve_batch(b.counts, b.woff, b.points, b.normals, b.mu, b.wrench, qps=qps,
                          beta=kw.get("beta", 1.0), kappa=kw.get("torque_scale", 20.0))
     assert np.abs(f[qps] - ref["forces"][qps][:, :3 * m]).max() <= 1e-4
+
+
+# no force reaches the limits: the same forces, to the rounding of 32 bits
+@pytest.mark.parametrize("m,s,grasps", [(4, 9, 60), (5, 9, 4700)])
+def test_force_limits_no_force_reaches(m, s, grasps):
+    b = wl.uniform_batch(795 + m, grasps, m, s)
+    print("newton: large force_max, m %d, %d QPs" % (m, b.n_qps), flush=True)
+    want = run_gpu(b, force_max=1e4)
+    top = np.abs(want["forces"]).max()
+    assert top < 1e3
+    for fmax in (1e8, 1e12, 1e30):
+        got = run_gpu(b, force_max=fmax)
+        assert np.all(got["status"] & api.ST_POLISHED)
+        assert np.abs(got["forces"] - want["forces"]).max() <= 2.0 ** -23 * top + 1e-6

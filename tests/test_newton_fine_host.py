@@ -26,7 +26,7 @@ def host(tmp_path_factory):
     return ctypes.CDLL(out)
 
 
-def _solve(host, b, beta, kappa, cone=False, max_steps=128):
+def _solve(host, b, beta, kappa, cone=False, max_steps=128, fmax=1.0):
     f, info = np.zeros((b.n_qps, 3 * b.m_max)), np.zeros((b.n_qps, 2), np.int32)
     ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)
     c = lambda a: np.ascontiguousarray(a, np.float64)
@@ -35,12 +35,12 @@ def _solve(host, b, beta, kappa, cone=False, max_steps=128):
         P, N, mu, T = c(b.points[g, :m]), c(b.normals[g, :m]), c(b.mu[g, :m]), c(beta * b.wrench[a:e].astype(float))
         ff, ii = np.zeros((e - a, 3 * m)), np.zeros((e - a, 2), np.int32)
         host.host_newton_fine(int(cone), m, ptr(P), ptr(N), ptr(mu), ptr(T), e - a, ctypes.c_double(kappa),
-                              ctypes.c_double(EPS), ctypes.c_double(1.0), max_steps, ptr(ff), ptr(ii))
+                              ctypes.c_double(EPS), ctypes.c_double(fmax), max_steps, ptr(ff), ptr(ii))
         f[a:e, :3 * m], info[a:e] = ff, ii
     return f, info
 
 
-def _exact(host, b, beta, kappa, f0, cone=False):
+def _exact(host, b, beta, kappa, f0, cone=False, fmax=1.0):
     f = np.zeros_like(f0)
     ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)
     c = lambda a: np.ascontiguousarray(a, np.float64)
@@ -51,7 +51,7 @@ def _exact(host, b, beta, kappa, f0, cone=False):
         P, N, mu, T = c(b.points[g, :m]), c(b.normals[g, :m]), c(b.mu[g, :m]), c(beta * b.wrench[w].astype(float))
         x0, x = c(f0[w, :3 * m]), np.zeros(3 * m)
         res = host.host_newton_exact(int(cone), m, ptr(P), ptr(N), ptr(mu), ptr(T), ctypes.c_double(kappa),
-                                     ctypes.c_double(EPS), ctypes.c_double(1.0), ptr(x0), ptr(x))
+                                     ctypes.c_double(EPS), ctypes.c_double(fmax), ptr(x0), ptr(x))
         assert res < 1e-20, "QP %d: |F| %.1e in 128 bits" % (w, res)
         f[w, :3 * m] = x
     return f
@@ -76,3 +76,15 @@ def test_cone_with_large_right_hand_sides(host, m, beta, kappa):
     f, info = _solve(host, b, beta, kappa, cone=True)
     assert np.all(info[:, 0] == 1)
     assert np.abs(f - _exact(host, b, beta, kappa, f, cone=True)).max() <= 2e-8
+
+
+# a force_max that stands for "no limit" (the forces stay below 200, rounded to
+# 32 bits by up to 8e-6)
+@pytest.mark.parametrize("cone", [False, True])
+@pytest.mark.parametrize("beta", [1.0, 1e-6])
+@pytest.mark.parametrize("fmax", [1e6, 1e10, 1e30])
+def test_force_limits_no_force_reaches(host, cone, beta, fmax):
+    b = wl.uniform_batch(36, 40, 5, 9)
+    f, info = _solve(host, b, beta, 20.0, cone=cone, fmax=fmax)
+    assert np.all(info[:, 0] == 1)
+    assert np.abs(f - _exact(host, b, beta, 20.0, f, cone=cone, fmax=fmax)).max() <= 1e-6 * beta
