@@ -224,8 +224,7 @@ def main():
                    "kkt_rel_max": float(np.max(kkt)),
                    "iters_mean": float(np.mean(iters)), "iters_p99": float(np.percentile(iters, 99)),
                    "finalize_ms": round(float(np.mean(fin_ms)), 4),
-                   "polish_chunk": "auto (%d for %d QPs)" % (
-                       api.bodex_qp_effective_params(p, db.n_qps)["polish_chunk"], db.n_qps),
+                   "polish_kind": api.bodex_qp_polish_kind(p, db.n_qps),
                    "step_device_ms_median": round(float(np.median(dev_ms)), 4),
                    "step_device_ms_p99": round(float(np.percentile(dev_ms, 99)), 4)},
         "roofline": roofline,
@@ -254,9 +253,8 @@ def forms(torch, api, wl):
     db3 = api.DeviceBatch(b3)
     s_max = int(np.max(np.diff(b3.woff)))
     side = torch.cuda.Stream()
-    # the autotuner's choice for this shape: polish chunk (one-lane budget
-    # before the contact-parallel polish), ADMM register budget, persistent
-    # cost-sorted launch or not; cached per shape class
+    # the autotuner's choice for this shape: which polish, ADMM register budget,
+    # persistent cost-sorted launch or not; cached per shape class
     base = api.default_params(m_max=5, s_max=s_max)
     t0 = time.perf_counter()
     knobs, table = autotune.tune(db3, base=base, reps=2)
@@ -277,14 +275,15 @@ def forms(torch, api, wl):
         side.synchronize()
         tb = (time.perf_counter() - t0) / n
         conv = int(np.sum((r3["status"].cpu().numpy() & api.ST_CONVERGED) != 0))
-        dflt = [t for t in table if t["knobs"] == {"polish_chunk": 20, "admm_waves": 2, "batched": 1}]
+        dflt = [t for t in table if t["knobs"]["polish_chunk"] != 0 and
+                t["knobs"]["admm_waves"] == 2 and t["knobs"]["batched"] == 1]
         res["batched"] = {"workload": "ellipsoid-m45-s6to32 (50,000 grasps, %d QPs)" % db3.n_qps,
                           "ms": round(tb * 1e3, 3), "qps_per_s": round(conv / tb, 1),
                           "converged": conv, "graph_replays": sb.stats()["graph_replays"],
-                          "knobs": knobs, "knobs_from": "autotune cache (%d configurations, %.1f s)" % (
-                              len(table), tune_s),
+                          "knobs": knobs, "polish_kind": api.bodex_qp_polish_kind(pb, db3.n_qps),
+                          "knobs_from": "autotune cache (%d configurations, %.1f s)" % (len(table), tune_s),
                           "tuning_best_ms": min(t["ms"] for t in table),
-                          "tuning_chunk20_batched_ms": dflt[0]["ms"] if dflt else None}
+                          "tuning_waves2_batched_ms": dflt[0]["ms"] if dflt else None}
         sb.close()
         # per-(m, s) plain launches of the same grasps
         groups = {}

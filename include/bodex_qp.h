@@ -280,13 +280,23 @@ size_t bodex_qp_state_bytes(int n_grasps, int n_qps, int m_max);
 /* The values the library takes for parameters whose rule it owns (see
  * admm_tol, check_every, max_iters and polish_chunk above), for a solve of
  * n_qps QPs with *p: ADMM's stopping tolerance, iteration cap and residual
- * check period, and the one-lane polish's factorisation budget (0: the
- * polish runs one lane per QP to the end, as for the circular cone, gamma > 0
- * or without BODEX_F_POLISH).  Needs no device.  Any output pointer may be
+ * check period, and the factorisation budget of the chunked polish, for where
+ * that runs (0: it does not apply to the circular cone, to gamma > 0 or without
+ * BODEX_F_POLISH); bodex_qp_polish_kind says which polish does.  Needs no device.  Any output pointer may be
  * NULL; BODEX_EINVAL (message in bodex_qp_last_error(NULL)) for invalid
  * parameters. */
 int bodex_qp_effective_params(const bodex_qp_params *p, int n_qps, float *admm_tol, int *max_iters,
                               int *check_every, int *polish_chunk);
+
+/* The polish that a solve or descent of n_qps QPs with *p runs (a BODEX_POLISH_*
+ * value; bodex_qp_solve_static runs the one-lane or the barrier polish), or
+ * BODEX_EINVAL as above.  Needs no device. */
+#define BODEX_POLISH_NONE 0     /* no BODEX_F_POLISH                         */
+#define BODEX_POLISH_ONE_LANE 1 /* active set, one lane per QP to the end    */
+#define BODEX_POLISH_CHUNKED 2  /* active set, budgeted, then contact-parallel */
+#define BODEX_POLISH_NEWTON 3   /* dual Newton; what it leaves, one-lane or barrier */
+#define BODEX_POLISH_BARRIER 4  /* circular cone: barrier                    */
+int bodex_qp_polish_kind(const bodex_qp_params *p, int n_qps);
 
 /* Statistics of the last solve (host copies, filled after the stream is
  * synchronised by this call): number of graph replays, refactorisations,

@@ -141,6 +141,8 @@ def lib():
                                                 ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int),
                                                 ctypes.POINTER(ctypes.c_int)]
         L.bodex_qp_effective_params.restype = ctypes.c_int
+        L.bodex_qp_polish_kind.argtypes = [ctypes.POINTER(Params), ctypes.c_int]
+        L.bodex_qp_polish_kind.restype = ctypes.c_int
         L.bodex_qp_kernel_times.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_float),
                                             ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_float)]
         L.bodex_qp_kernel_times.restype = ctypes.c_int
@@ -163,7 +165,8 @@ EXPORTED = ("bodex_qp_default_params", "bodex_qp_create", "bodex_qp_set_stream",
             "bodex_qp_solve", "bodex_qp_solve_static", "bodex_qp_backward", "bodex_qp_destroy",
             "bodex_qp_last_error", "bodex_qp_state_bytes", "bodex_qp_last_stats",
             "bodex_qp_kernel_times", "bodex_qp_detach_energy", "bodex_qp_contact_query",
-            "bodex_qp_pose_gradient", "bodex_qp_descend", "bodex_qp_effective_params")
+            "bodex_qp_pose_gradient", "bodex_qp_descend", "bodex_qp_effective_params",
+            "bodex_qp_polish_kind")
 
 
 def default_params(**overrides) -> Params:
@@ -181,12 +184,22 @@ def default_params(**overrides) -> Params:
 
 def bodex_qp_effective_params(p: Params, n_qps: int) -> dict:
     """The values the library takes for the parameters whose rule it owns:
-    ADMM's tolerance, iteration cap and check period, and the polish's
+    ADMM's tolerance, iteration cap and check period, and the chunked polish's
     factorisation budget, for a solve of n_qps QPs (no device needed)."""
     tol, mi, ce, pc = ctypes.c_float(), ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     _check(lib().bodex_qp_effective_params(ctypes.byref(p), int(n_qps), ctypes.byref(tol), ctypes.byref(mi),
                                            ctypes.byref(ce), ctypes.byref(pc)))
     return {"admm_tol": tol.value, "max_iters": mi.value, "check_every": ce.value, "polish_chunk": pc.value}
+
+
+POLISH_KINDS = ("none", "one-lane", "chunked", "newton", "barrier")  # BODEX_POLISH_*
+
+
+def bodex_qp_polish_kind(p: Params, n_qps: int) -> str:
+    """The polish a solve of n_qps QPs runs, by name (no device needed)."""
+    k = lib().bodex_qp_polish_kind(ctypes.byref(p), int(n_qps))
+    _check(min(k, 0))
+    return POLISH_KINDS[k]
 
 
 def admm_check_period(p: Params) -> int:

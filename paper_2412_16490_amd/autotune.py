@@ -8,8 +8,9 @@ knobs and keeps the fastest configuration whose results are all converged:
                    shape: one lane per QP, 64 QPs per wavefront) before it is
                    handed to the contact-parallel polish (group shape: one
                    lane per contact, 8 or 16 QPs per wavefront); 0 keeps every
-                   QP in the one-lane polish, 1 hands nearly all on.  Where
-                   the dual Newton polish applies, every value but 0 takes it;
+                   QP in the one-lane polish, 1 hands nearly all on.  Values
+                   that select the same polish (the dual Newton polish, where
+                   it applies, takes every value but 0) are timed once;
 * ``admm_waves``   register budget of the ADMM kernel as resident waves per
                    SIMD (1 = no cap, 2, 3, 4): trades spills for occupancy;
 * ``check_every``  iterations between residual checks / rho updates;
@@ -78,7 +79,7 @@ def tune(batch: api.DeviceBatch, base: api.Params | None = None, reps: int = 3,
     grid = grid or DEFAULT_GRID
     s_max = int(np.max(np.diff(batch.woff)))
     stream = torch.cuda.Stream()
-    table = []
+    table, seen = [], set()
     names = list(grid)
     for combo in itertools.product(*[grid[n] for n in names]):
         knobs = dict(zip(names, combo))
@@ -86,6 +87,12 @@ def tune(batch: api.DeviceBatch, base: api.Params | None = None, reps: int = 3,
         p.m_max = batch.m_max
         p.s_max = max(p.s_max, s_max)
         p = apply(p, knobs)
+        kind = api.bodex_qp_polish_kind(p, batch.n_qps)
+        key_run = (kind, p.polish_chunk if kind == "chunked" else None,
+                   *(v for n, v in knobs.items() if n != "polish_chunk"))
+        if key_run in seen:
+            continue
+        seen.add(key_run)
         ms, ok = _time_solve(p, batch, reps, stream)
         table.append({"knobs": knobs, "ms": round(ms * 1e3, 4), "converged": ok})
     good = [t for t in table if t["converged"]] or table

@@ -1134,6 +1134,16 @@ int bodex_qp_kernel_times(bodex_qp_t* h, float* admm_ms, float* finalize_ms, flo
     return rc;
 }
 
+int bodex_qp_polish_kind(const bodex_qp_params* p, int n_qps) {
+    if (!p || n_qps < 0) return fail(nullptr, BODEX_EINVAL, "params is NULL or n_qps < 0");
+    const int rc = validate_params(p, nullptr);
+    if (rc) return rc;
+    if (!(p->flags & BODEX_F_POLISH)) return BODEX_POLISH_NONE;
+    if (newton_applies(*p, n_qps)) return BODEX_POLISH_NEWTON;
+    if (p->friction_cone == BODEX_CONE_CIRCULAR) return BODEX_POLISH_BARRIER;
+    return effective(*p, n_qps).polish_chunk > 0 ? BODEX_POLISH_CHUNKED : BODEX_POLISH_ONE_LANE;
+}
+
 int bodex_qp_effective_params(const bodex_qp_params* p, int n_qps, float* admm_tol, int* max_iters,
                                int* check_every, int* polish_chunk) {
     if (!p || n_qps < 0) return fail(nullptr, BODEX_EINVAL, "params is NULL or n_qps < 0");
