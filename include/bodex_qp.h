@@ -21,11 +21,13 @@
  * KKT matrix per grasp shared by all of its wrenches, an affine step plus a
  * clamp per iteration, periodic residual checks with per-grasp step-size
  * adaptation -- followed by an FP64 polish to the exact minimiser.  For the
- * pyramid with gamma = 0 that is a semismooth Newton method on the QP's
- * six-dimensional dual; what it leaves, and the other forms, go to a polish
- * that re-solves the reduced KKT system on the identified active set and
- * corrects that set with dual active-set steps, keeping the polished point
- * only when its KKT conditions hold.
+ * pyramid with gamma = 0, and for small batches of the circular cone, that is
+ * a semismooth Newton method on the QP's six-dimensional dual; what it leaves,
+ * and the other forms, go (pyramid) to a polish that re-solves the reduced KKT
+ * system on the identified active set and corrects that set with dual
+ * active-set steps, keeping the polished point only when its KKT conditions
+ * hold, or (cone) to a barrier method.  bodex_qp_polish_kind names the polish
+ * of given parameters.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -87,9 +89,16 @@ extern "C" {
  *   mu cos(pi/8)).
  * CIRCULAR: the exact cone |(f_2, f_3)| <= mu f_1 of Eq. 1 (the quadratically
  *   constrained form the paper linearises).  ADMM projects each contact's
- *   force onto the cone truncated at fmax (closed form); the FP64 polish is a
+ *   force onto the cone truncated at fmax (closed form).  The FP64 polish of a
+ *   solve of up to 8192 QPs with gamma = 0, eps_reg >= 5e-7 and polish_chunk
+ *   not 0 is the dual Newton method, otherwise (and for what that leaves) a
  *   barrier (interior-point) method warm-started from the ADMM point.  The
- *   ADMM state has 3 m_max + 1 rows of z and y (rows 3i..3i+2 contact i's
+ *   Newton forces are the minimiser's to 1e-7 fmax; the barrier's, in weakly
+ *   determined directions, are off by more than 1e-5 fmax in one QP of a
+ *   thousand, more than 1e-4 in 20 of a million (5 contacts, 1.2 million QPs),
+ *   up to 2e-3.  So a grasp's forces can differ by as much between a small and
+ *   a large batch; polish_chunk 0 takes the barrier at every size.
+ *   The ADMM state has 3 m_max + 1 rows of z and y (rows 3i..3i+2 contact i's
  *   force, row 3 m_max the normal-sum row).  bodex_qp_backward uses the
  *   polished forces the solve left in state.x. */
 #define BODEX_CONE_PYRAMID8 0
@@ -128,7 +137,8 @@ typedef struct {
                           /* is also handed on at its next factorisation once */
                           /* at most 8 lanes of its wavefront still polish.   */
                           /* Used with BODEX_F_POLISH, the pyramid and        */
-                          /* gamma = 0.                                       */
+                          /* gamma = 0 (and, 0 or not, by the circular cone:  */
+                          /* see BODEX_CONE_CIRCULAR).                        */
     unsigned flags;       /* BODEX_F_*                                        */
     int admm_waves;       /* ADMM kernel register budget as resident waves   */
                           /* per SIMD: 1, 2, 3 or 4 (0 = by batch size)        */

@@ -402,16 +402,18 @@ hipError_t launch(Kind k, int mm, const KArgs& a, int grid, size_t lds, hipStrea
 
 // Dual Newton polish (bodex_newton.h), without the normal-sum row, unless
 // polish_chunk 0 asks for the one-lane kernels: for the pyramid, and for the
-// circular cone up to kConeNewtonQps QPs.  eps at least 5e-7: the method's
-// forces carry the rounding of |beta t| / eps (1e-16 of 1e6 at the default
-// 1e-6); below that the polishes that work in the forces are the more accurate.
+// circular cone up to kConeNewtonQps QPs.  eps at least 5e-7: below that the
+// rounding of |beta t| / eps spoils u at workload sizes too, which the polishes
+// that work in the forces do not carry (since newton_fine ends such QPs the
+// line could lie lower; not measured).
 // The cone's limit is not one of speed (barrier / Newton polish: 384 QPs 1.53 /
-// 0.07 ms, 131,072 QPs 9.0 / 0.5 ms) but of equal results: about two QPs in a
-// million leave the barrier polish 3e-4 to 2e-3 off the minimiser in weakly
-// determined force directions (60 batches of 131,072 QPs, against 64 bits;
-// the Newton polish of the same QPs: 1e-7), so that below the limit a batch
-// sees a difference beyond the force tolerance's scale in one of 60 cases at
-// most, and large batches keep the forces they had.
+// 0.07 ms, 131,072 QPs, with the limit off, 9.0 / 0.5 ms) nor of accuracy (the
+// header states both), but of equal results: about two QPs in a million leave
+// the barrier polish 3e-4 to 2e-3 off the minimiser in weakly determined force
+// directions (60 batches of 131,072 QPs, against 64 bits; the Newton polish of
+// the same QPs: 1e-7), so that below the limit a batch sees a difference beyond
+// the force tolerance's scale in one of 60 cases at most, and large batches
+// keep the forces they had.
 constexpr int kConeNewtonQps = 8192;
 // Under a smaller step cap the pyramid's Newton solves leave QPs in every tile to
 // the one-lane polish, and both cost more than the chunked polish alone does.
