@@ -119,8 +119,9 @@ __device__ inline int newton_info(const NewtonOut& o) {
                unsigned(min(o.slopes, 16383)) << 18);
 }
 // The word of QP w (of the cone: until its objective is written).
+template <bool CONE>
 __device__ __forceinline__ int newton_word(const KArgs& a, int w) {
-    return a.ninfo ? a.ninfo[w] : __float_as_int(a.qobj[w]);
+    return CONE ? __float_as_int(a.qobj[w]) : a.ninfo[w];
 }
 // Whether the outputs of QP w are still to come from the finalize launch: only
 // they set the bit, ADMM's status never holds it.
@@ -996,7 +997,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BODEX_F
             if (!skip) {
                 if (ran) {
                     if (a.pflops)
-                        a.pflops[w] = float(polish_flops(si.m, po) + (rest ? newton_info_flops(si.m, newton_word(a, w)) : 0.0));
+                        a.pflops[w] = float(polish_flops(si.m, po) + (rest ? newton_info_flops(si.m, newton_word<false>(a, w)) : 0.0));
                     if (po.status == 0) {
                         polished = true;
                         st |= kStPolished;
@@ -1292,7 +1293,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) co
                 }
                 if (a.pflops)
                     a.pflops[w] = float(cone_polish_flops(si.m, po) +
-                                        (rest ? newton_info_flops(si.m, newton_word(a, w)) : 0.0));
+                                        (rest ? newton_info_flops(si.m, newton_word<true>(a, w)) : 0.0));
                 if (po.status == 0) {
                     polished = true;
                     st |= kStPolished;

@@ -569,12 +569,14 @@ BODEX_FI NewtonOut newton_solve(const NewtonStore<NC>& st, const NewtonFriction 
     st.end() = kNewtonTol * sqrt(t2) + 1e-12 * fmin(fm, 1.0) * fmin(1e3 * sqrt(t2), 1.0) + 1e-24;
     group_sum<GS>(len);
     st.scale() = len[0] / m;
-    // the rounding of u / eps; times a row of G that of y, times its square that of F
     {
-        const double noise = 0x1p-53 * sqrt(t2) / eps;
-        const bool fine = noise * sqrt(st.scale()) > kFineForce || noise * st.scale() > kNewtonTol * sqrt(t2);
+        // 2^-53 |beta t| / eps is the rounding of u / eps, times a row of G that
+        // of y, times its square that of F (compared squared: no root or
+        // division on the way of the QPs that it does not concern)
+        const double sc = st.scale();
+        const bool fine = 0x1p-106 * t2 * sc > kFineForce * kFineForce * eps * eps || 0x1p-53 * sc > kNewtonTol * eps;
         st.fine() = fine ? 1.0 : 0.0;
-        st.tol() = fine ? fmax(st.end(), kFineTol * noise * st.scale()) : st.end();
+        st.tol() = fine ? fmax(st.end(), kFineTol * 0x1p-53 * sqrt(t2) / eps * sc) : st.end();
     }
     const ProxSchedule first = CONE ? kProxCone : kProxPyramid;
     st.ratio() = first.ratio;

@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) ne
         const int w = si.w0 + j;
         const size_t W_ = size_t(a.sW), sw = state_col(a, si, j);
         unsigned char st = a.status[w];
-        const int info = newton_word(a, w);
+        const int info = newton_word<CONE>(a, w);
         const bool finite_in = good && !(st & kStNonfinite);
         double bt[6];
 #pragma unroll
