@@ -32,7 +32,8 @@ __device__ __forceinline__ double cone_kept(const KArgs& a, int c, size_t sw) {
 // a tile are separate workgroups, so a hard QP holds up no more than the
 // other groups of its wave.  Bound by FP64 issue and the dependent chain of
 // the 6 x 6 factor and of the slopes; HBM traffic is the ADMM point in (12 m B
-// per QP) and u out (52 B).  The contacts' geometry, the proximal centre and the
+// per QP) and u out (52 B; the forces, 24 m B, of QPs that newton_fine ended and
+// of the cone).  The contacts' geometry, the proximal centre and the
 // group's scalars are in LDS: an early form with everything in registers (256,
 // and spills) took 1105 us at 5 contacts and 131,072 QPs, with these in LDS 862
 // (8 lanes per QP) and 734 (2 lanes).  At 629 us now (2 lanes), it and
@@ -145,13 +146,13 @@ __device__ inline NewtonRows newton_rows(int face, const NewtonFold& Y, double N
     return L;
 }
 
-// Outputs: forces and multipliers from u, objective, energy, the ADMM-form
+// Outputs: forces and multipliers from u (or from the stored forces), objective, energy, the ADMM-form
 // state of the point and its relative KKT residual (rel_kkt64's, of the
 // rounded state, without reading it back).  Streams the state out: 4 (6 m +
 // 18 m) B per QP at the pyramid's nine rows per contact.  QPs the Newton
 // method left are counted in KArgs::nfail and keep their ADMM point; their
 // outputs come from the finalize launch that follows.  Bound by HBM writes; at
-// three waves per SIMD (160 registers) nothing spills, at four 140 B a lane
+// three waves per SIMD (166 registers) nothing spills, at four 140 B a lane
 // did: 5 contacts, 131,072 QPs 43 -> 35 us, 951,279 QPs 417 -> 347, 8 contacts,
 // 8547 QPs 36 -> 22.
 template <int MM, bool CONE>
